@@ -156,7 +156,10 @@ int debye_plan_destroy(debye_plan *plan);
 
 /* Override the schedule's frequency split (lanes per candidate along the
  * frequency axis, a power of two; 0 restores the automatic choice) for pole
- * count n_poles (0 = all). Used by the autotuner and the tests.  Re-tiling
+ * count n_poles (0 = all). Used by the autotuner and the tests.  Pole counts
+ * split over four lanes (17 and more) keep at least four frequency lanes in the
+ * kernel: a narrower split sets their tiles, each run as several waves, with
+ * the results of split 4.  Re-tiling
  * (here or in debye_plan_autotune) makes the plan's next optimiser run
  * re-capture its graph.  Not while work of the plan is in flight. */
 int debye_plan_set_freq_split(debye_plan *plan, int32_t n_poles, int32_t split);
@@ -181,7 +184,8 @@ int debye_plan_get_launch(const debye_plan *plan);
 
 /* Autotune the schedule on real data: for every pole-count bucket without an
  * override, time `reps` launches (1..100) of the cost kernel at each frequency
- * split (1, 2, 4, ... up to 64 / pole split, while spectra keep at least 8
+ * split (1, 2, 4, ... up to 64 / pole split, from 4 for pole counts split over
+ * four lanes, while spectra keep at least 8
  * points per lane) with HIP events on `stream`, after about 30 ms of warm-up
  * launches and in three rounds (the best time of each split counts), and keep
  * the fastest (a wider split must be at least 3 % faster than the best

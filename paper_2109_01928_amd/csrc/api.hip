@@ -57,7 +57,8 @@ int set_error(int code, const char *msg) { return fail(code, "%s", msg); }
 }  // namespace dfit
 
 struct Bucket {
-  int32_t N = 0, SP = 1, SF = 1, cpw = 64;
+  int32_t N = 0, SP = 1, SF = 1;
+  int32_t lane_sf = 1, cpw = 64;   // frequency lanes per candidate in the kernel (>= SF), candidates per wave
   int64_t n_cands = 0, n_tiles = 0, max_f = 0, work = 0;
   int64_t xcd_off[9] = {};   // tiles of XCD x: xcd_off[x] .. xcd_off[x+1]-1
   bool uni = false;          // split 1 and every tile holds one material: wave-uniform spectra loads
@@ -114,6 +115,11 @@ void free_bucket(Bucket &b) {
   b.d_lane_cand = b.d_lane_mat = b.d_mats = nullptr;
 }
 
+// Fewest frequency lanes a candidate can have in the kernel: the four-lane
+// pole split sums four points in one matrix instruction.  A narrower split
+// set for such a bucket keeps its tiles, each run as several waves.
+int min_split(int SP) { return SP == 4 ? 4 : 1; }
+
 int pick_split(const debye_plan &p, const Bucket &b) {
   auto it = p.sf_override.find(b.N);
   if (it == p.sf_override.end()) it = p.sf_override.find(0);
@@ -124,7 +130,7 @@ int pick_split(const debye_plan &p, const Bucket &b) {
   // smallest power of two that gives TARGET_WAVES waves, without splitting
   // short spectra below 16 points per lane
   const int64_t avg_f = b.n_cands ? b.work / (b.n_cands * b.N) : 1;
-  int sf = 1;
+  int sf = min_split(b.SP);
   while (sf < max_sf && (b.n_cands * b.SP * sf + 63) / 64 < TARGET_WAVES && avg_f / (2 * sf) >= 16) sf *= 2;
   // the SP > 1 path keeps each candidate's normal matrix in LDS: fewer
   // candidates per wave until two waves per SIMD fit
@@ -211,9 +217,10 @@ int build_tiles(debye_plan &p, Bucket &b) {
   ++p.sched_gen;
   free_bucket(b);
   b.SF = pick_split(p, b);
-  b.cpw = 64 / (b.SP * b.SF);
+  b.lane_sf = std::max(b.SF, min_split(b.SP));
+  b.cpw = 64 / (b.SP * b.lane_sf);
   const Schedule sc = make_schedule(p.f_off.data(), p.cand_off.data(), b.mats, b.N, b.SP, b.SF);
-  for (int x = 0; x < 9; ++x) b.xcd_off[x] = sc.xcd_off[x];
+  for (int x = 0; x < 9; ++x) b.xcd_off[x] = sc.xcd_off[x] * (b.lane_sf / b.SF);
   b.uni = sc.uni;
   const std::vector<int32_t> &lc = sc.lane_cand, &lm = sc.lane_mat;
   b.n_tiles = (int64_t)lc.size() / b.cpw;
@@ -223,15 +230,16 @@ int build_tiles(debye_plan &p, Bucket &b) {
   // executed instructions (Gram accumulators, basis values, ring moves,
   // the other passes), plus the dense solve
   {
-    const int SP = b.SP, NB = (b.N + SP - 1) / SP, D = SP == 1 ? 0 : NB * SP / 2;
-    const int NG = SP == 1 ? b.N * (b.N + 1) / 2 : NB * (D + 1);
+    const int SP = b.SP, NB = (b.N + SP - 1) / SP, D = SP == 2 ? NB : 0;
+    // (a matrix instruction takes the pipe for four issue slots)
+    const int NG = SP == 1 ? b.N * (b.N + 1) / 2 : SP == 2 ? NB * (D + 1) : 4 * (NB * (NB + 1) / 2);
     const double per_point = NG + 12.0 * NB + 60.0 + (SP > 1 ? 2.0 * D + 24.0 : 0.0);
     b.tile_est.assign(b.n_tiles, 0.0f);
     for (int64_t t = 0; t < b.n_tiles; ++t) {
       int64_t fmax = 0;
       for (int64_t l = t * b.cpw; l < (t + 1) * b.cpw; ++l)
         if (lc[l] >= 0) fmax = std::max(fmax, p.f_off[lm[l] + 1] - p.f_off[lm[l]]);
-      b.tile_est[t] = (float)((double)((fmax + b.SF - 1) / b.SF) * per_point + 0.5 * (double)b.N * b.N * b.N);
+      b.tile_est[t] = (float)((double)((fmax + b.lane_sf - 1) / b.lane_sf) * per_point + 0.5 * (double)b.N * b.N * b.N);
     }
   }
   if (hipMalloc(&b.d_lane_cand, lc.size() * 4) != hipSuccess || hipMalloc(&b.d_lane_mat, lm.size() * 4) != hipSuccess ||
@@ -260,7 +268,7 @@ int build_ragged(debye_plan &p) {
   std::vector<std::vector<std::pair<float, int64_t>>> per_xcd(8);
   for (size_t i = 0; i < p.buckets.size(); ++i) {
     const Bucket &bk = p.buckets[i];
-    rb[i] = dfit::RaggedBucket{bk.N, bk.SF, bk.cpw, bk.uni ? 1 : 0, bk.d_lane_cand, bk.d_lane_mat};
+    rb[i] = dfit::RaggedBucket{bk.N, bk.lane_sf, bk.cpw, bk.uni ? 1 : 0, bk.d_lane_cand, bk.d_lane_mat};
     p.ragged_lds = std::max(p.ragged_lds, (size_t)dfit::lds_bytes_per_candidate(bk.N) * bk.cpw);
     for (int x = 0; x < 8; ++x)
       for (int64_t t = bk.xcd_off[x]; t < bk.xcd_off[x + 1]; ++t)
@@ -346,7 +354,7 @@ dfit::FitArgs fit_args(const debye_plan *p, const Bucket &bk, const debye_batch 
   a.ld = ld;
   a.damping = damping;
   a.flags = flags;
-  a.freq_split = bk.SF;
+  a.freq_split = bk.lane_sf;
   a.cand_per_wave = bk.cpw;
   a.lane_cand = bk.d_lane_cand;
   a.lane_mat = bk.d_lane_mat;
@@ -648,8 +656,8 @@ int debye_plan_autotune(debye_plan *p, const debye_batch *b, const double *log10
     if (!bk.n_cands || p->sf_override.count(bk.N) || p->sf_override.count(0)) continue;
     const int64_t avg_f = bk.work / (bk.n_cands * bk.N);
     std::vector<int> splits;
-    for (int sf = 1; sf <= 64 / bk.SP; sf *= 2) {
-      if (sf > 1 && avg_f / sf < 8) break;
+    for (int sf = min_split(bk.SP); sf <= 64 / bk.SP; sf *= 2) {
+      if (sf > min_split(bk.SP) && avg_f / sf < 8) break;
       splits.push_back(sf);
     }
     // bring the clocks up first (about 30 ms of this bucket's work), so that

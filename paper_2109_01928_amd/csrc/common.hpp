@@ -28,6 +28,15 @@ __device__ __forceinline__ double rcp_nr(double d) {
   return __builtin_fma(r, __builtin_fma(e, e, e), r);
 }
 
+// 1 / sqrt(d) of a normal positive d: the hardware estimate r0 (relative error
+// below 2^-24) and one third-order step r0 (1 + e/2 + 3 e^2/8), e = 1 - d r0^2,
+// which leaves an error of order e^3 before the final rounding.
+__device__ __forceinline__ double rsq_nr(double d) {
+  const double r = __builtin_amdgcn_rsq(d);
+  const double e = __builtin_fma(-(d * r), r, 1.0);
+  return __builtin_fma(r * e, __builtin_fma(e, 0.375, 0.5), r);
+}
+
 // Cross-lane move of a double inside a quad (DPP quad_perm; CTRL encodes the
 // source lane of each of the four lanes, two bits per lane).
 // Every source lane of a quad permutation is valid, so the move needs no

@@ -25,14 +25,35 @@
 //     one reciprocal), pass 3 evaluates the model sums as rational functions
 //     of w^2 (basis form as the fallback), and the adjoint adds pass 4.
 //
-// Ring split of the Gram matrix for SP > 1 poles-per-lane groups: the NP =
-// NB*SP (padded) poles are placed on a ring; lane q owns poles q*NB .. q*NB+NB-1
-// and accumulates, for each owned pole p and each offset d = 0..NP/2, the
-// entry G(p, (p+d) mod NP).  Every unordered pair is covered (the d = NP/2
-// entries twice, with bit-identical values), the work is balanced, and a lane
-// only needs the basis values of the next NP/2 poles on the ring, which it
-// receives from its neighbours by DPP quad permutes.  Padded poles get tau = 0,
-// so their loss column is exactly zero and they drop out.
+// Gram matrix on the two-lane split (SP = 2): the NP = 2 NB (padded) poles are
+// placed on a ring; lane q owns poles q*NB .. q*NB+NB-1 and accumulates, for
+// each owned pole p and each offset d = 0..NP/2, the entry G(p, (p+d) mod NP).
+// Every unordered pair is covered (the d = NP/2 entries twice, with
+// bit-identical values), the work is balanced, and a lane only needs the basis
+// values of the next NP/2 poles on the ring, which it receives from its
+// neighbour by DPP quad permutes.  Padded poles get tau = 0, so their loss
+// column is exactly zero and they drop out.
+//
+// Gram matrix on the four-lane split (SP = 4, N >= 17): 4x4 tiles of poles on
+// the matrix cores, v_mfma_f64_4x4x4 (four blocks; D += A B per block, K = 4
+// points).  Its lanes are numbered pole (bits 0-1), block (bits 2-3), point
+// (bits 4-5) in A and in B alike, so a lane that forms the basis of poles
+// q, 4 + q, 8 + q, ... at its point holds the operands of every tile as they
+// are: no value moves between lanes, and the accumulators are one register
+// pair a tile (15 at N = 20) where the ring held 55.  The instruction takes
+// the FP64 pipe for 16 cycles (four issue slots): 60 slots a wave and point
+// for the tiles at N = 20, against 75 for the ring's 55 fused multiply-adds
+// and 20 moves; alone it sustained 68.6 TFLOP/s, chains of fused multiply-adds
+// 62.7, the two mixed 71 to 74.  A candidate's lanes hold at least four points
+// (SF >= 4), so a wave holds at most four candidates, and the solves are shared
+// by 16 lanes (Coop).  Both against the ring with SF = 2 and solves run by
+// every lane, forward evaluation of N = 20 on one box: F = 4096 (32,768
+// candidates) 3.06 -> 2.69 ms, F = 200 (131,072) 1.18 -> 0.87 ms, F = 50 0.92
+// -> 0.58 ms; N = 17 at F = 4096 3.00 -> 2.71 ms, N = 24 3.88 -> 3.35 ms; the
+// adjoint at N = 20, F = 4096, 6.00 -> 5.45 ms.  At N = 12 to 16 the padding
+// to whole tiles and the smaller reciprocal groups of a lane cost more than
+// the ring's moves (F = 2000: N = 12 1.49 ms on the ring, 1.71 on tiles; N = 16
+// 2.12 and 2.15).
 
 #pragma once
 
@@ -43,11 +64,13 @@ namespace dfit {
 
 template <int N, int SP> struct Shape {
   static_assert(SP == 1 || SP == 2 || SP == 4, "pole split must be 1, 2 or 4");
+  static constexpr bool MF = SP == 4;                        // Gram on the matrix cores
   static constexpr int NB = (N + SP - 1) / SP;               // poles owned per lane
-  static constexpr int NP = NB * SP;                         // padded ring size
-  static constexpr int D = (SP == 1) ? 0 : NP / 2;           // ring half width
-  static constexpr int NV = (SP == 1) ? N : NB + D;          // basis values seen by a lane
-  static constexpr int NG = (SP == 1) ? N * (N + 1) / 2 : NB * (D + 1);  // Gram accumulators
+  static constexpr int NP = NB * SP;                         // padded pole count
+  static constexpr int D = (SP == 2) ? NP / 2 : 0;           // ring half width
+  static constexpr int NV = (SP == 2) ? NB + D : NB;         // basis values seen by a lane
+  // Gram accumulators: the triangle, the tiles' upper triangle, or the ring's
+  static constexpr int NG = (SP == 1) ? N * (N + 1) / 2 : MF ? NB * (NB + 1) / 2 : NB * (D + 1);
   static constexpr int NT = N * (N + 1) / 2;                 // packed triangle
   // per candidate: the parked factor (SP == 1), or the whole solve (SP > 1)
   static constexpr int LDS_DOUBLES = (SP == 1) ? N * (N + 1) / 2 : N * (N + 1) / 2 + 5 * N;
@@ -55,13 +78,17 @@ template <int N, int SP> struct Shape {
 
 constexpr __host__ __device__ int tri(int n, int i, int j) { return i * n - (i * (i - 1)) / 2 + (j - i); }
 
-// value of block t (owned by lane (q + t) mod SP) of a lane's ring view
-template <int SP> __device__ __forceinline__ double ring_fetch(double v, int t) {
-  if constexpr (SP == 2) {
-    return dpp_quad<QP_SWAP1>(v);
-  } else {
-    return t == 1 ? dpp_quad<QP_ROT1>(v) : dpp_quad<QP_SWAP2>(v);
-  }
+// the neighbour's value on the two-lane ring
+__device__ __forceinline__ double ring_fetch(double v) { return dpp_quad<QP_SWAP1>(v); }
+
+// xor mask, in the wave's lane numbers, of bit m of a lane's index among its
+// candidate's lanes: the same number, except on the four-lane split, whose
+// lanes are numbered as the matrix instruction has them (pole lane in bits
+// 0-1, block in bits 2-3, point in bits 4-5) and a candidate's lanes by pole
+// lane, point, block
+template <int SP> __device__ __forceinline__ int lane_mask(int m) {
+  if constexpr (SP == 4) return m < 4 ? m : m < 16 ? m << 2 : m >> 2;
+  else return m;
 }
 
 // sum over the SP lanes of a candidate (bit-identical in all of them)
@@ -76,9 +103,10 @@ template <int SP> __device__ __forceinline__ double group_sum(double v) {
   }
 }
 
-// sum over the SF frequency lanes of a candidate (xor butterfly)
-__device__ __forceinline__ double freq_sum(double v, int sp, int s_lanes) {
-  for (int m = sp; m < s_lanes; m <<= 1) v += __shfl_xor(v, m, WAVE);
+// sum over the SF frequency lanes of a candidate (xor butterfly over bits
+// from .. s_lanes / 2 of the lane's index among its candidate's lanes)
+template <int SP> __device__ __forceinline__ double freq_sum(double v, int from, int s_lanes) {
+  for (int m = from; m < s_lanes; m <<= 1) v += __shfl_xor(v, lane_mask<SP>(m), WAVE);
   return v;
 }
 
@@ -86,14 +114,15 @@ __device__ __forceinline__ double freq_sum(double v, int sp, int s_lanes) {
 // crossbar; issued eight at a time, they wait for it once per eight values
 // instead of once per value (value by value, the additions and so the
 // results are those of freq_sum).
-template <int K> __device__ __forceinline__ void freq_sum_n(double *v, int sp, int s_lanes) {
-  for (int m = sp; m < s_lanes; m <<= 1) {
+template <int K, int SP> __device__ __forceinline__ void freq_sum_n(double *v, int from, int s_lanes) {
+  for (int m = from; m < s_lanes; m <<= 1) {
+    const int lm = lane_mask<SP>(m);
 #pragma unroll
     for (int e0 = 0; e0 < K; e0 += 8) {
       double o[8];
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        if (e0 + e < K) o[e] = __shfl_xor(v[e0 + e], m, WAVE);
+        if (e0 + e < K) o[e] = __shfl_xor(v[e0 + e], lm, WAVE);
 #pragma unroll
       for (int e = 0; e < 8; ++e)
         if (e0 + e < K) v[e0 + e] += o[e];
@@ -116,16 +145,18 @@ __device__ __forceinline__ void kahan_fma_acc(double &sum, double &c, double a, 
 // lanes, the exchanges issued together as in freq_sum_n; hi[e] receives the
 // sum rounded to a double.  TwoSum's error term does not depend on the
 // operand order, so all lanes end with the same bits.
-template <int K> __device__ __forceinline__ void freq_sum_dd_n(double *hi, const double *lo_in, int sp, int s_lanes) {
+template <int K, int SP>
+__device__ __forceinline__ void freq_sum_dd_n(double *hi, const double *lo_in, int from, int s_lanes) {
   double lo[K];
 #pragma unroll
   for (int e = 0; e < K; ++e) lo[e] = lo_in[e];
-  for (int m = sp; m < s_lanes; m <<= 1) {
+  for (int m = from; m < s_lanes; m <<= 1) {
+    const int lm = lane_mask<SP>(m);
     double oh[K], ol[K];
 #pragma unroll
     for (int e = 0; e < K; ++e) {
-      oh[e] = __shfl_xor(hi[e], m, WAVE);
-      ol[e] = __shfl_xor(lo[e], m, WAVE);
+      oh[e] = __shfl_xor(hi[e], lm, WAVE);
+      ol[e] = __shfl_xor(lo[e], lm, WAVE);
     }
 #pragma unroll
     for (int e = 0; e < K; ++e) {
@@ -582,6 +613,158 @@ template <int N> __device__ __noinline__ void lds_chol_solve(lds_cptr A, lds_cpt
   }
 }
 
+// Orders a wave's LDS accesses across its lanes: the LDS serves one wave's
+// accesses in order, so only the compiler has to keep it.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// The factorisation and the solves shared by 16 lanes of a candidate (the
+// four-lane split, whose candidates hold 16, 32 or 64 lanes; lanes with the
+// same c do the same work).  Lane c has rows and columns c and c + 16 of the
+// matrix and elements c and c + 16 of the vectors; a lane without one takes
+// the last.  With every lane running the whole factorisation, its N^3 / 6
+// fused multiply-adds and their operands' LDS reads took as long as 200 points
+// of the frequency passes at N = 20.
+template <int N> struct Coop {
+  static constexpr int N0 = N < 16 ? N : 16, N1 = N > 16 ? N : 0;   // rows of the first and second column
+  static constexpr int NX = N1 > 0 ? N1 : 1;
+  lds_ptr A, uinv;
+  int k0, k1, src;   // own elements; byte address of the candidate's first lane for ds_bpermute
+  __device__ __forceinline__ Coop(lds_ptr A_, lds_ptr uinv_, int c, int first_lane)
+      : A(A_), uinv(uinv_), k0(c < N ? c : N - 1), k1(c + 16 < N ? c + 16 : N - 1), src(first_lane * 4) {}
+
+  // lane c's value in all lanes of the candidate
+  __device__ __forceinline__ double from(double v, int c) const {
+    const int at = src + 4 * ((c & 3) + ((c >> 2) << 4));
+    return __hiloint2double(__builtin_amdgcn_ds_bpermute(at, __double2hiint(v)),
+                            __builtin_amdgcn_ds_bpermute(at, __double2loint(v)));
+  }
+
+  // Equilibrates the packed triangle A (its diagonal becomes 1 + damping),
+  // factors it A = U^T U in place (off-diagonal; reciprocal pivots to uinv)
+  // and takes x <- U^-T D^-1 b along.  Step j: every lane posts its row-j
+  // entries, reads the row back, and takes the outer product off its columns,
+  // a_ik -= a_ji (a_jk / a_jj): a serial chain of N LDS round trips.
+  __device__ __forceinline__ bool factor(lds_cptr b, lds_ptr invd, lds_ptr rowbuf, lds_ptr xbuf, double damping,
+                                         double tol, double &x0, double &x1) const {
+    double c0[N0], c1[NX];
+    // own columns (entries below the diagonal are other columns', never used)
+#pragma unroll
+    for (int i = 0; i < N0; ++i) c0[i] = A[tcol(0, k0) + i];
+#pragma unroll
+    for (int i = 0; i < N1; ++i) c1[i] = A[tcol(0, k1) + i];
+    const double d0 = 1.0 / sqrt(A[tcol(k0, k0)]);
+    invd[k0] = d0;
+    x0 = b[k0] * d0;
+    double d1 = 0.0;
+    x1 = 0.0;
+    if constexpr (N1 > 0) {
+      d1 = 1.0 / sqrt(A[tcol(k1, k1)]);
+      invd[k1] = d1;
+      x1 = b[k1] * d1;
+    }
+    wave_sync();
+    bool ok = true;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const double di = invd[i];
+      ok = ok && di > 0.0 && di < INFINITY;   // 0 < g_ii < inf
+      if (i < N0) c0[i] = k0 == i ? 1.0 + damping : c0[i] * di * d0;
+      if (i < N1) c1[i] = k1 == i ? 1.0 + damping : c1[i] * di * d1;
+    }
+#pragma unroll
+    for (int j = 0; j < N; ++j) {
+      if (j < N0) {
+        rowbuf[k0] = c0[j];
+        xbuf[k0] = x0;
+      }
+      if (j < N1) {
+        rowbuf[k1] = c1[j];
+        xbuf[k1] = x1;
+      }
+      wave_sync();
+      double r[N];
+#pragma unroll
+      for (int i = j; i < N; ++i) r[i] = rowbuf[i];
+      const double xj = xbuf[j];
+      wave_sync();
+      ok = ok && r[j] > tol;
+      const double ri = rcp_nr(r[j]), ui = rsq_nr(r[j]);
+      uinv[j] = ui;
+      if (j < N0) {
+        const double v = c0[j] * ri, u = c0[j] * ui;
+        if (k0 > j) {
+          A[tcol(0, k0) + j] = u;
+          x0 = __builtin_fma(-v, xj, x0);
+        }
+#pragma unroll
+        for (int i = j + 1; i < N0; ++i) c0[i] = __builtin_fma(-r[i], v, c0[i]);
+      }
+      if (j < N1) {
+        const double v = c1[j] * ri, u = c1[j] * ui;
+        if (k1 > j) {
+          A[tcol(0, k1) + j] = u;
+          x1 = __builtin_fma(-v, xj, x1);
+        }
+#pragma unroll
+        for (int i = j + 1; i < N1; ++i) c1[i] = __builtin_fma(-r[i], v, c1[i]);
+      }
+    }
+    wave_sync();
+    x0 *= uinv[k0];
+    if constexpr (N1 > 0) x1 *= uinv[k1];
+    return ok;
+  }
+
+  // x <- U^-T x
+  __device__ __forceinline__ void forward(double &x0, double &x1) const {
+    const double u0 = uinv[k0], u1 = N1 > 0 ? uinv[k1] : 0.0;
+    double c0[N0], c1[NX];   // own columns above the diagonal
+#pragma unroll
+    for (int l = 0; l < N0; ++l) c0[l] = l < k0 ? A[tcol(0, k0) + l] : 0.0;
+#pragma unroll
+    for (int l = 0; l < N1; ++l) c1[l] = l < k1 ? A[tcol(0, k1) + l] : 0.0;
+#pragma unroll
+    for (int l = 0; l < N - 1; ++l) {
+      const double y = from(l < 16 ? x0 * u0 : x1 * u1, l & 15);
+      if (l < N0) x0 = __builtin_fma(-c0[l], y, x0);
+      if (l < N1) x1 = __builtin_fma(-c1[l], y, x1);
+    }
+    x0 *= u0;
+    if constexpr (N1 > 0) x1 *= u1;
+  }
+
+  // x <- U^-1 x
+  __device__ __forceinline__ void backward(double &x0, double &x1) const {
+    const double u0 = uinv[k0], u1 = N1 > 0 ? uinv[k1] : 0.0;
+    double r0[N], r1[N];   // own rows right of the diagonal
+#pragma unroll
+    for (int k = 1; k < N; ++k) r0[k] = k > k0 ? A[tcol(k0, k)] : 0.0;
+#pragma unroll
+    for (int k = 17; k < N; ++k) r1[k] = k > k1 ? A[tcol(k1, k)] : 0.0;
+#pragma unroll
+    for (int k = N - 1; k > 0; --k) {
+      const double z = from(k < 16 ? x0 * u0 : x1 * u1, k & 15);
+      x0 = __builtin_fma(-r0[k], z, x0);
+      if (k > 16) x1 = __builtin_fma(-r1[k], z, x1);
+    }
+    x0 *= u0;
+    if constexpr (N1 > 0) x1 *= u1;
+  }
+
+  // the lane's elements of a vector in LDS
+  __device__ __forceinline__ void get(lds_cptr v, double &x0, double &x1) const {
+    x0 = v[k0];
+    x1 = N1 > 0 ? v[k1] : 0.0;
+  }
+  __device__ __forceinline__ void put(lds_ptr v, double x0, double x1) const {
+    v[k0] = x0;
+    if constexpr (N1 > 0) v[k1] = x1;
+  }
+};
+
 // per-candidate LDS region of the SP > 1 path: packed triangle, then five
 // vectors of N (scaling, reciprocal pivots, rhs, two work vectors)
 template <int N> struct LdsLayout {
@@ -725,23 +908,36 @@ template <int N, int SP, bool GRAD, int UNI, bool XR = false>
 __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   static_assert(!(XR && GRAD), "the extended-precision refinement is a forward-kernel form");
   using S = Shape<N, SP>;
+  constexpr bool MF = S::MF;
   constexpr int NB = S::NB, NV = S::NV, NG = S::NG, D = S::D;
   extern __shared__ double lds_all[];
 
   const int lane = threadIdx.x;
   const int SF = UNI == 1 ? 1 : a.freq_split;
   const int SL = SP * SF;            // lanes per candidate
-  const int grp = lane / SL;         // candidate slot in the wave
-  const int sub = lane - grp * SL;
+  // candidate slot in the wave, the lane's index among the candidate's lanes,
+  // its pole lane and its frequency lane.  On the four-lane split (SF a
+  // multiple of 4) a candidate holds SF / 4 of the wave's four blocks of 16
+  // lanes, each of four pole lanes and four points (see lane_mask).
+  const int grp = MF ? ((lane >> 2) & 3) / (SF >> 2) : lane / SL;
+  const int sub = MF ? (lane & 3) + ((lane >> 4) << 2) + ((((lane >> 2) & 3) & ((SF >> 2) - 1)) << 4) : lane - grp * SL;
+  const int first_lane = MF ? grp * (SF >> 2) * 4 : grp * SL;   // of the candidate
   const int q = sub % SP;            // pole block
   const int fl = UNI == 1 ? 0 : sub / SP; // frequency lane
+  // owned pole cI: consecutive poles, or every fourth on the four-lane split
+  // (lane q holds row or column q of every tile of four poles)
+  auto pole_of = [](int own, int cI) -> int { return MF ? 4 * cI + own : own * NB + cI; };
   const int64_t slot = tile * a.cand_per_wave + grp;
   const int32_t cand = a.lane_cand[slot];
   const bool active = cand >= 0;
-  const int32_t mat = active ? a.lane_mat[slot] : 0;
+  // (inactive lanes of the four-lane split take the first slot's spectrum, so
+  // that their wave's point counts are those of its candidates)
+  const int32_t mat = active ? a.lane_mat[slot] : MF ? a.lane_mat[tile * a.cand_per_wave] : 0;
   const int64_t c = active ? cand : 0;
   // a wave whose candidates all belong to materials marked done exits
   // before any work (wave-uniform: a block is one wave)
+  if constexpr (MF)   // (a wave of a split narrower than its lanes can hold padding alone)
+    if (__builtin_amdgcn_ballot_w64(active) == 0) return;
   if (a.skip_mat && __builtin_amdgcn_ballot_w64(active && a.skip_mat[mat] == 0) == 0) return;
 
   int64_t f0 = 0, F = 0;
@@ -749,7 +945,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     const int32_t mu = __builtin_amdgcn_readfirstlane(a.lane_mat[tile * a.cand_per_wave]);
     f0 = a.f_off[mu];
     F = a.f_off[mu + 1] - f0;
-  } else if (active) {
+  } else if (active || MF) {
     f0 = a.f_off[mat];
     F = a.f_off[mat + 1] - f0;
   }
@@ -781,7 +977,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   bool bad = false;
 #pragma unroll
   for (int cI = 0; cI < NB; ++cI) {
-    const int p = q * NB + cI;
+    const int p = pole_of(q, cI);
     tau[cI] = 0.0;
     if (p < N && active) {
       const double t = a.theta[c * a.ld + p];
@@ -822,14 +1018,21 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     Sv[cI] = 0.0;
   }
   double sum_er = 0.0;
-  // one point of the Gram pass
   // one point of the Gram pass, from its basis values Iv[0 .. NB-1]
   auto gram_acc = [&](double *Iv, double er, double ei) {
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) bv[cI] = __builtin_fma(Iv[cI], ei, bv[cI]);
-    if constexpr (SP > 1) {
+    if constexpr (MF) {
+      // tile (I, J) of four poles by four: the lane's Iv[I] is its row of A
+      // (pole 4 I + q at the lane's point), Iv[J] its column of B
 #pragma unroll
-      for (int v = NB; v < NV; ++v) Iv[v] = ring_fetch<SP>(Iv[v % NB], v / NB);
+      for (int I = 0; I < NB; ++I)
+#pragma unroll
+        for (int J = I; J < NB; ++J)
+          G[tri(NB, I, J)] = __builtin_amdgcn_mfma_f64_4x4x4f64(Iv[I], Iv[J], G[tri(NB, I, J)], 0, 0, 0);
+    } else if constexpr (SP == 2) {
+#pragma unroll
+      for (int v = NB; v < NV; ++v) Iv[v] = ring_fetch(Iv[v % NB]);
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI)
 #pragma unroll
@@ -850,13 +1053,62 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   // Two points per trip let the reciprocal chains of their bases interleave.
   // With no DPP in the body (SP == 1) the compiler pairs the points itself.
   // The ring's DPP moves are convergent operations, which the compiler does
-  // not unroll into a loop with a remainder, so on the pole-split path the
+  // not unroll into a loop with a remainder, so on the two-lane split the
   // pair is written out where it fits the register budget at two waves per
-  // SIMD: four pole lanes up to N = 20 (228 VGPRs at N = 20), two up to
-  // N = 14 (the general-tile form from N = 13 on, N = 15, 16 and N > 20
+  // SIMD: up to N = 14 (the general-tile form from N = 13 on and N = 15, 16
   // spill with it).
-  constexpr bool PAIR_RING = (SP == 4 && N <= 20) || (SP == 2 && (N == 12 || (N <= 14 && UNI != 0)));
-  if constexpr (!PAIR_RING) {
+  constexpr bool PAIR_RING = SP == 2 && (N == 12 || (N <= 14 && UNI != 0));
+  if constexpr (MF) {
+    // The matrix instruction takes every lane of the wave, so the trips are
+    // counted for the whole wave: n_full of them give every lane two points of
+    // its own, the rest (one, where the tile is uniform) lets a lane without
+    // a point run at w = 0, whose U is 0.
+    int64_t n_full = F / (2 * SF), n_all = (F + 2 * SF - 1) / (2 * SF);
+    if constexpr (UNI == 0) {
+#pragma unroll
+      for (int m = 4; m < 16; m <<= 1) {   // over the blocks, hence the candidates
+        const int64_t of = __shfl_xor(n_full, m, WAVE), oa = __shfl_xor(n_all, m, WAVE);
+        n_full = of < n_full ? of : n_full;
+        n_all = oa > n_all ? oa : n_all;
+      }
+      auto uniform = [](int64_t v) -> int64_t {
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)((uint64_t)v >> 32));
+        return (int64_t)(((uint64_t)hi << 32) | lo);
+      };
+      n_full = uniform(n_full);
+      n_all = uniform(n_all);
+    }
+    int64_t k = fl, t = 0;
+    if (n_full > 0) {
+      double wa_n = ld_first(om, k), era_n = ld_first(epr, k), eia_n = ld_first(epi, k);
+      double wb_n = ld_first(om, k + SF), erb_n = ld_first(epr, k + SF), eib_n = ld_first(epi, k + SF);
+      for (; t < n_full; ++t, k += 2 * SF) {
+        const double wa = wa_n, era = era_n, eia = eia_n, wb = wb_n, erb = erb_n, eib = eib_n;
+        // in-bounds prefetch of the next two points, no branch
+        const int64_t ka = (k + 2 * SF < F) ? k + 2 * SF : k, kb = (k + 3 * SF < F) ? k + 3 * SF : k;
+        wa_n = ld(om, ka);
+        era_n = ld(epr, ka);
+        eia_n = ld(epi, ka);
+        wb_n = ld(om, kb);
+        erb_n = ld(epr, kb);
+        eib_n = ld(epi, kb);
+        double Ia[NV], Ib[NV];
+        basis_Us2<NB>(wa, wb, tau2s, sq, Ia, Ib);
+        gram_acc(Ia, era, eia);
+        gram_acc(Ib, erb, eib);
+      }
+    }
+    for (; t < n_all; ++t, k += 2 * SF) {
+      const bool va = k < F, vb = k + SF < F;
+      const int64_t ka = va ? k : F - 1, kb = vb ? k + SF : F - 1;
+      const double wa = va ? ld(om, ka) : 0.0, wb = vb ? ld(om, kb) : 0.0;
+      double Ia[NV], Ib[NV];
+      basis_Us2<NB>(wa, wb, tau2s, sq, Ia, Ib);
+      gram_acc(Ia, va ? ld(epr, ka) : 0.0, va ? ld(epi, ka) : 0.0);
+      gram_acc(Ib, vb ? ld(epr, kb) : 0.0, vb ? ld(epi, kb) : 0.0);
+    }
+  } else if constexpr (!PAIR_RING) {
     int64_t k = fl;
     double w_n = 0, er_n = 0, ei_n = 0;
     if (k < F) {
@@ -871,24 +1123,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       w_n = ld(om, kn);
       er_n = ld(epr, kn);
       ei_n = ld(epi, kn);
-      double Iv[NV];
-      basis_Us<NB>(w, w * w, tau2s, sq, Iv);
-#pragma unroll
-      for (int cI = 0; cI < NB; ++cI) bv[cI] = __builtin_fma(Iv[cI], ei, bv[cI]);
-      if constexpr (SP > 1) {
-#pragma unroll
-        for (int v = NB; v < NV; ++v) Iv[v] = ring_fetch<SP>(Iv[v % NB], v / NB);
-#pragma unroll
-        for (int cI = 0; cI < NB; ++cI)
-#pragma unroll
-          for (int d = 0; d <= D; ++d) G[cI * (D + 1) + d] = __builtin_fma(Iv[cI], Iv[cI + d], G[cI * (D + 1) + d]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-#pragma unroll
-          for (int j = i; j < N; ++j) G[tri(N, i, j)] = __builtin_fma(Iv[i], Iv[j], G[tri(N, i, j)]);
-      }
-      sum_er += er;
+      gram_point(w, er, ei);
     }
   } else {
     // the odd point last; the pole lanes of a candidate share their
@@ -922,28 +1157,28 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     }
     if (k < F) gram_point(wa_n, era_n, eia_n);
   }
-  freq_sum_n<NG>(G, SP, SL);
-  if constexpr (SP > 1) {
+  freq_sum_n<NG, SP>(G, MF ? 16 : SP, SL);   // (the four points of a block are summed by the matrix instruction)
+  if constexpr (SP == 2) {
     double tv[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) tv[v] = v < NB ? ts[v] : ring_fetch<SP>(ts[v % NB], v / NB);
+    for (int v = 0; v < NV; ++v) tv[v] = v < NB ? ts[v] : ring_fetch(ts[v % NB]);
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI)
 #pragma unroll
       for (int d = 0; d <= D; ++d) G[cI * (D + 1) + d] *= ts[cI] * tv[cI + d];
-  } else {
+  } else if constexpr (SP == 1) {
 #pragma unroll
     for (int i = 0; i < N; ++i)
 #pragma unroll
       for (int j = i; j < N; ++j) G[tri(N, i, j)] *= ts[i] * ts[j];
   }
-  freq_sum_n<NB>(bv, SP, SL);
+  freq_sum_n<NB, SP>(bv, SP, SL);
 #pragma unroll
   for (int cI = 0; cI < NB; ++cI) {
     bv[cI] = bv[cI] * ts[cI];
     bad = bad || !(fabs(bv[cI]) < INFINITY);
   }
-  sum_er = freq_sum(sum_er, SP, SL);
+  sum_er = freq_sum<SP>(sum_er, SP, SL);
   bad = bad || !(fabs(sum_er) < INFINITY);
   bad = group_sum<SP>(bad ? 1.0 : 0.0) != 0.0;
 
@@ -981,8 +1216,33 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     L = lds_all + (int64_t)grp * S::LDS_DOUBLES;
     const LdsLayout<N> lay(L);
     double *A = lay.A, *invd = lay.invd, *uinv = lay.uinv, *vb = lay.vb, *vz = lay.vz;
+    if constexpr (MF) {
+      // the lane holds element (row lane >> 4, column q) of every tile; the
+      // rows' factors tau s come through LDS
+      double *st = lay.vw;
 #pragma unroll
-    for (int cI = 0; cI < NB; ++cI) {
+      for (int cI = 0; cI < NB; ++cI) {
+        const int p = pole_of(q, cI);
+        if (p < N) {
+          st[p] = ts[cI];
+          vb[p] = bv[cI];
+        }
+      }
+      __syncthreads();
+      const int row = lane >> 4;
+#pragma unroll
+      for (int I = 0; I < NB; ++I) {
+        const int r = 4 * I + row;
+        const double tr = r < N ? st[r] : 0.0;
+#pragma unroll
+        for (int J = I; J < NB; ++J) {
+          const int c2 = 4 * J + q;
+          if (c2 < N && r <= c2) A[tcol(r, c2)] = G[tri(NB, I, J)] * (tr * ts[J]);
+        }
+      }
+    }
+#pragma unroll
+    for (int cI = 0; cI < (MF ? 0 : NB); ++cI) {
       const int p1 = q * NB + cI;
 #pragma unroll
       for (int d = 0; d <= D; ++d) {
@@ -996,13 +1256,21 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       if (p1 < N) vb[p1] = bv[cI];
     }
     __syncthreads();
-    ok = lds_equilibrate_factor<N>((lds_ptr)A, (lds_ptr)invd, (lds_ptr)uinv, damping, tol);
-    for (int i = 0; i < N; ++i) vz[i] = vb[i] * invd[i];
-    lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vz);
+    if constexpr (MF) {
+      const Coop<N> coop((lds_ptr)A, (lds_ptr)uinv, sub & 15, first_lane);
+      double x0, x1;
+      ok = coop.factor((lds_cptr)vb, (lds_ptr)invd, (lds_ptr)lay.vw, (lds_ptr)vz, damping, tol, x0, x1);
+      coop.backward(x0, x1);
+      coop.put((lds_ptr)vz, x0, x1);
+    } else {
+      ok = lds_equilibrate_factor<N>((lds_ptr)A, (lds_ptr)invd, (lds_ptr)uinv, damping, tol);
+      for (int i = 0; i < N; ++i) vz[i] = vb[i] * invd[i];
+      lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vz);
+    }
     __syncthreads();
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
-      const int p = q * NB + cI;
+      const int p = pole_of(q, cI);
       zt[cI] = p < N ? vz[p] : 0.0;
       invd_own[cI] = p < N ? invd[p] : 0.0;
     }
@@ -1034,7 +1302,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     double th[NB], tl[NB];
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
-      const int p = q * NB + cI;
+      const int p = pole_of(q, cI);
       th[cI] = 0.0;   // padded poles: x = 0, so I = 0
       tl[cI] = 0.0;
       if (p < N && active) {
@@ -1089,7 +1357,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         }
       }
     }
-    freq_sum_dd_n<NB>(gv, gl, SP, SL);
+    freq_sum_dd_n<NB, SP>(gv, gl, SP, SL);
   } else if constexpr (!GRAD && (SP == 4 || (SP == 2 && NB <= 6))) {
     if (refine) {
       // The pole splits run this pass over pairs of owner lanes: lane q takes
@@ -1116,13 +1384,13 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       auto pole = [&](int e) -> int {
         const int own = 2 * h + (e < 8 * NQ ? e / (4 * NQ) : (e - 8 * NQ) / (LO > 0 ? LO : 1));
         const int cI = e < 8 * NQ ? e % (4 * NQ) : 4 * NQ + (e - 8 * NQ) % (LO > 0 ? LO : 1);
-        return own * NB + cI;
+        return pole_of(own, cI);
       };
       const LdsLayout<N> lay(L);
       double *st2 = lay.vb, *stz = lay.vw;
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
-        const int p = q * NB + cI;
+        const int p = pole_of(q, cI);
         if (p < N) {   // (every frequency lane of the owner writes the same values)
           st2[p] = tau2s[cI];
           stz[p] = zc[cI] * ts[cI];
@@ -1184,7 +1452,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         double ngc[H];
 #pragma unroll
         for (int e = 0; e < H; ++e) ngc[e] = -gc[e];
-        freq_sum_dd_n<H>(gh, ngc, HP, SL);   // the point subsets and the frequency lanes
+        freq_sum_dd_n<H, SP>(gh, ngc, HP, SL);   // the point subsets and the frequency lanes
       }
       __syncthreads();
 #pragma unroll
@@ -1195,7 +1463,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       __syncthreads();
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
-        const int p = q * NB + cI;
+        const int p = pole_of(q, cI);
         gv[cI] = (p < N ? st2[p] : 0.0) * ts[cI];
       }
     }
@@ -1290,9 +1558,9 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       double ngl[NB];
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) ngl[cI] = -gl[cI];
-      freq_sum_dd_n<NB>(gv, ngl, SP, SL);
+      freq_sum_dd_n<NB, SP>(gv, ngl, SP, SL);
     }
-    if constexpr (GRAD) freq_sum_n<NB>(Sv, SP, SL);
+    if constexpr (GRAD) freq_sum_n<NB, SP>(Sv, SP, SL);
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
       gv[cI] = gv[cI] * ts[cI];
@@ -1316,15 +1584,24 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       double *A = lay.A, *uinv = lay.uinv, *vw = lay.vw;
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
-        const int p = q * NB + cI;
+        const int p = pole_of(q, cI);
         if (p < N) vw[p] = __builtin_fma(gv[cI], invd_own[cI], -damping * zt[cI]);
       }
       __syncthreads();
-      lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vw);
+      if constexpr (MF) {
+        const Coop<N> coop((lds_ptr)A, (lds_ptr)uinv, sub & 15, first_lane);
+        double x0, x1;
+        coop.get((lds_cptr)vw, x0, x1);
+        coop.forward(x0, x1);
+        coop.backward(x0, x1);
+        coop.put((lds_ptr)vw, x0, x1);
+      } else {
+        lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vw);
+      }
       __syncthreads();
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
-        const int p = q * NB + cI;
+        const int p = pole_of(q, cI);
         zt[cI] += p < N ? vw[p] : 0.0;
       }
     }
@@ -1443,7 +1720,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         __syncthreads();
 #pragma unroll
         for (int cI = 0; cI < NB; ++cI) {
-          const int p = q * NB + cI;
+          const int p = pole_of(q, cI);
           if (p < N) {
             t2s[p] = tau2_of(cI);
             wsh[p] = wv_[cI];
@@ -1461,9 +1738,9 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       red_from = SP;
     }
   }
-  cost = freq_sum(cost, red_from, SL);
+  cost = freq_sum<SP>(cost, red_from, SL);
   if constexpr (!GRAD) {
-    sa = freq_sum(sa, red_from, SL);
+    sa = freq_sum<SP>(sa, red_from, SL);
     if (F > 0) {
       cost -= sa * (sa / (double)F);
       einf = shift + sa / (double)F;
@@ -1482,7 +1759,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   if (writer && a.weights) {
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
-      const int p = q * NB + cI;
+      const int p = pole_of(q, cI);
       if (p < N) a.weights[c * a.ld + p] = st == ST_OK ? wv_[cI] : NAN;
     }
   }
@@ -1492,8 +1769,8 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     // ---- adjoint: mu = M^-1 (s o g_w), M = D A D
     if (a.grad_cost) gc = active ? a.grad_cost[c] : 0.0;
     double mt[NB], mu[NB];
-    freq_sum_n<NB>(gw2, SP, SL);
-    freq_sum_n<NB>(gw, SP, SL);
+    freq_sum_n<NB, SP>(gw2, SP, SL);
+    freq_sum_n<NB, SP>(gw, SP, SL);
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
       gw[cI] = -2.0 * pole_scale<NB>(sq, cI) * __builtin_fma(tau_of(cI), gw2[cI], gw[cI]);
@@ -1509,15 +1786,24 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       double *A = lay.A, *uinv = lay.uinv, *vw = lay.vw;
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
-        const int p = q * NB + cI;
+        const int p = pole_of(q, cI);
         if (p < N) vw[p] = mt[cI];
       }
       __syncthreads();
-      lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vw);
+      if constexpr (MF) {
+        const Coop<N> coop((lds_ptr)A, (lds_ptr)uinv, sub & 15, first_lane);
+        double x0, x1;
+        coop.get((lds_cptr)vw, x0, x1);
+        coop.forward(x0, x1);
+        coop.backward(x0, x1);
+        coop.put((lds_ptr)vw, x0, x1);
+      } else {
+        lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vw);
+      }
       __syncthreads();
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
-        const int p = q * NB + cI;
+        const int p = pole_of(q, cI);
         mt[cI] = p < N ? vw[p] : 0.0;
       }
     }
@@ -1578,10 +1864,10 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         }
       }
     }
-    freq_sum_n<NB>(T1, SP, SL);
-    freq_sum_n<NB>(T2, SP, SL);
-    freq_sum_n<NB>(T3, SP, SL);
-    freq_sum_n<NB>(T4, SP, SL);
+    freq_sum_n<NB, SP>(T1, SP, SL);
+    freq_sum_n<NB, SP>(T2, SP, SL);
+    freq_sum_n<NB, SP>(T3, SP, SL);
+    freq_sum_n<NB, SP>(T4, SP, SL);
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
       T1[cI] = LN10 * T1[cI];
@@ -1595,7 +1881,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         for (int64_t p = N; p < a.ld; ++p) a.grad_theta[c * a.ld + p] = 0.0;
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
-        const int p = q * NB + cI;
+        const int p = pole_of(q, cI);
         if (p >= N) continue;
         double g = -2.0 * wv_[cI] * T1[cI] + mu[cI] * T2[cI] - zc[cI] * T3[cI] -
                    2.0 * damping * mu[cI] * zc[cI] * T4[cI];
@@ -1646,8 +1932,8 @@ void fit_dd_kernel(const FitArgs a) {
 // pole count alone, autotuned frequency split): one lane per candidate up to
 // N = 11 (at N = 9..11 its register spills cost less than the DPP traffic and
 // the padded pole of the two-lane ring; at N = 12 they do not), two lanes up
-// to N = 16 (N = 13..16 pad to 16 on four lanes), four above (two lanes
-// spill the adjoint heavily at N = 17, 18).
+// to N = 16, four above, with the Gram matrix on the matrix cores (figures at
+// the top of the file).
 constexpr int pole_split_for(int n) { return n <= 11 ? 1 : (n <= 16 ? 2 : 4); }
 
 // Blocks of a cost-kernel grid: eight times the longest of the 8 XCD tile
@@ -1669,9 +1955,10 @@ template <int N, bool GRAD> hipError_t launch_fit_variant(const FitArgs &a, int6
   b.n_tiles = n_tiles;
   const unsigned blocks = fit_grid_blocks(a);
   if (blocks == 0) return hipSuccess;
-  if (uni && a.freq_split == 1)
-    hipLaunchKernelGGL((fit_kernel<N, SP, GRAD, 1>), dim3(blocks), dim3(64), lds, s, b);
-  else if (uni)
+  if (uni && a.freq_split == 1) {
+    if constexpr (!Shape<N, SP>::MF)
+      hipLaunchKernelGGL((fit_kernel<N, SP, GRAD, 1>), dim3(blocks), dim3(64), lds, s, b);
+  } else if (uni)
     hipLaunchKernelGGL((fit_kernel<N, SP, GRAD, 2>), dim3(blocks), dim3(64), lds, s, b);
   else
     hipLaunchKernelGGL((fit_kernel<N, SP, GRAD, 0>), dim3(blocks), dim3(64), lds, s, b);

@@ -376,3 +376,33 @@ def test_empty_materials_and_determinism(D, orc):
     c1 = D.fit_eval(plan, b, th)[0].clone()
     c2 = D.fit_eval(plan, b, th)[0].clone()
     assert torch.equal(c1, c2)
+
+
+@pytest.mark.parametrize("N", [17, 20, 24])
+def test_split_below_four_lanes_runs_as_split_four(D, orc, N):
+    """The four-lane pole split keeps four frequency lanes: tiles of a narrower
+    split are run four candidates at a time, with the results of split 4 bit for
+    bit (70 and 12 candidates a material: tiles padded and shared by two
+    materials; spectra of different lengths in one wave)."""
+    import torch
+    Fm, Pm = [173, 40, 7, 256], [70, 12, 1, 33]
+    kind, params = W.draw_mixed(4, 600 + N, 1e6, 1e10)
+    lb, ub = W.tau_bounds(1e6, 1e10)
+    om = np.concatenate([W.log_grid(1e6, 1e10, f) for f in Fm])
+    wl = W.Workload(f"narrow splits N{N}", kind, params, W.offsets(Fm), om, np.full(4, N, np.int32),
+                    W.offsets(Pm), np.full(4, lb), np.full(4, ub), 1, seed=600 + N)
+    theta = W.draw_theta(wl.cand_off, wl.n_poles, wl.lb, wl.ub, wl.ld, seed=N)
+    b = _gpu_batch(D, wl, *targets_oracle(orc, wl))
+    th = torch.tensor(theta, device="cuda")
+    out = {}
+    for split in (1, 2, 4):
+        plan = D.Plan(b)
+        plan.set_freq_split(split)
+        assert plan.info()[0]["freq_split"] == split
+        c, g, _, _, st = D.fit_eval_grad(plan, b, th)
+        out[split] = [*D.fit_eval(plan, b, th), c, g, st]
+    torch.cuda.synchronize()
+    for split in (1, 2):
+        for x, y in zip(out[split], out[4]):
+            assert torch.equal(torch.nan_to_num(x), torch.nan_to_num(y)), split
+    _check_eval(D, orc, wl, theta, split=1, tag=f"narrow N{N}")
