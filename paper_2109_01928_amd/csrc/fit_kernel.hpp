@@ -73,7 +73,7 @@ template <int N, int SP> struct Shape {
   static constexpr int NG = (SP == 1) ? N * (N + 1) / 2 : MF ? NB * (NB + 1) / 2 : NB * (D + 1);
   static constexpr int NT = N * (N + 1) / 2;                 // packed triangle
   // per candidate: the parked factor (SP == 1), or the whole solve (SP > 1)
-  static constexpr int LDS_DOUBLES = (SP == 1) ? N * (N + 1) / 2 : N * (N + 1) / 2 + 5 * N;
+  static constexpr int LDS_DOUBLES = (SP == 1) ? N * (N + 1) / 2 : N * (N + 1) / 2 + (MF ? 6 : 5) * N;
 };
 
 constexpr __host__ __device__ int tri(int n, int i, int j) { return i * n - (i * (i - 1)) / 2 + (j - i); }
@@ -637,7 +637,11 @@ template <int N> struct Coop {
 
   // lane c's value in all lanes of the candidate
   __device__ __forceinline__ double from(double v, int c) const {
-    const int at = src + 4 * ((c & 3) + ((c >> 2) << 4));
+    // (the address is formed at each use: 16 of them kept in registers across
+    // the refinement pass would spill)
+    int at = src;
+    asm volatile("" : "+v"(at));
+    at += 4 * ((c & 3) + ((c >> 2) << 4));
     return __hiloint2double(__builtin_amdgcn_ds_bpermute(at, __double2hiint(v)),
                             __builtin_amdgcn_ds_bpermute(at, __double2loint(v)));
   }
@@ -766,14 +770,14 @@ template <int N> struct Coop {
 };
 
 // per-candidate LDS region of the SP > 1 path: packed triangle, then five
-// vectors of N (scaling, reciprocal pivots, rhs, two work vectors)
+// vectors of N (scaling, reciprocal pivots, rhs, two work vectors); on the
+// four-lane split a sixth (tau s)
 template <int N> struct LdsLayout {
   static constexpr int NT = N * (N + 1) / 2;
-  static constexpr int DOUBLES = NT + 5 * N;
-  double *A, *invd, *uinv, *vb, *vz, *vw;
+  double *A, *invd, *uinv, *vb, *vz, *vw, *vt;
   __device__ __forceinline__ explicit LdsLayout(double *base)
       : A(base), invd(base + NT), uinv(base + NT + N), vb(base + NT + 2 * N), vz(base + NT + 3 * N),
-        vw(base + NT + 4 * N) {}
+        vw(base + NT + 4 * N), vt(base + NT + 5 * N) {}
 };
 
 // factor parked by the SP == 1 path: A (off-diagonal) and reciprocal pivots
@@ -790,6 +794,142 @@ __device__ __forceinline__ void unpark(const double *park, int cpw, int grp, dou
 }
 
 // --------------------------------------------------------------------------
+// Reading a spectrum.  A lane takes points k0, k0 + stride, ... of its
+// candidate's spectrum, in every pass; the passes that read one point ahead
+// use the loops below.
+// --------------------------------------------------------------------------
+// How (WALK): 0, a lane's own 64-bit index; 1, the same, wave-uniform (split 1:
+// scalar loads); 2, a wave-uniform point and a lane's own constant offset; 3,
+// a lane's own 32-bit offset.
+// point k
+template <int WALK> __device__ __forceinline__ double ld(const double *p, int64_t k) {
+  if constexpr (WALK >= 2) return *(const double *)((const char *)p + ((uint32_t)k << 3));
+  else return p[k];
+}
+// The first point of a pass that reads one point ahead, through the constant
+// address space (the spectra are read-only during a launch).  Loads from two
+// address spaces are not merged, so the compiler keeps the loop's loads one
+// point ahead instead of folding them with this one into a single load at the
+// top of every trip (which would expose the load latency at each point).
+template <int WALK> __device__ __forceinline__ double ld_first(const double *p, int64_t k) {
+  using cptr = const __attribute__((address_space(4))) double *;
+  if constexpr (WALK >= 2) return *(cptr)((const char *)p + ((uint32_t)k << 3));
+  else return ((cptr)p)[k];
+}
+// Uniform tiles with a frequency split: the wave's lanes walk together, so a
+// point is a spectrum's base (a buffer descriptor), a wave-uniform byte offset
+// kept by the scalar unit, and a lane's own offset, which never changes: no
+// vector instruction forms an address.  (A lane's own index, clamped to stay
+// in bounds one trip ahead, and its 64-bit addresses took 9 of the 78 vector
+// instructions of a pair of points in the Gram pass at N = 20, and 8 of 86 in
+// the cost pass at N = 8.)
+struct Reader {
+  __amdgpu_buffer_rsrc_t r;
+  uint32_t lane;   // the lane's byte offset
+  __device__ __forceinline__ Reader(const double *p, int64_t F, int64_t k0)
+      : r(__builtin_amdgcn_make_buffer_rsrc((void *)p, 0, (int)(uint32_t)(F << 3), 0x00027000)),
+        lane((uint32_t)k0 << 3) {}
+  // the lane's point of the trip at point u
+  __device__ __forceinline__ double operator()(int32_t u) const {
+    return __builtin_bit_cast(double, __builtin_amdgcn_raw_buffer_load_b64(r, (int)lane, (int)((uint32_t)u << 3), 0));
+  }
+};
+
+struct Spectrum {
+  const double *om, *er, *ei;
+  int64_t F;
+};
+
+// body(w, eps', eps'') at points k0, k0 + stride, ... (k0 < stride)
+template <int WALK, int UNROLL, class BODY>
+__device__ __forceinline__ void each_point(const Spectrum &sp, int k0, int stride, BODY &&body) {
+  const int64_t F = sp.F;
+  int64_t k = k0;
+  if constexpr (WALK == 2) {
+    const int32_t n = (int32_t)F & ~(stride - 1);   // points of the trips every lane takes
+    const Reader om(sp.om, F, k0), er_(sp.er, F, k0), ei_(sp.ei, F, k0);
+    if (n > 0) {
+      double w_n = ld_first<WALK>(sp.om, k0), er_n = ld_first<WALK>(sp.er, k0), ei_n = ld_first<WALK>(sp.ei, k0);
+#pragma unroll UNROLL
+      for (int32_t u = 0; u < n; u += stride) {
+        const double w = w_n, er = er_n, ei = ei_n;
+        const int32_t un = u + stride < n ? u + stride : u;   // in-bounds prefetch, no branch
+        w_n = om(un);
+        er_n = er_(un);
+        ei_n = ei_(un);
+        body(w, er, ei);
+      }
+    }
+    k += n;
+    if (k < F) body(ld<WALK>(sp.om, k), ld<WALK>(sp.er, k), ld<WALK>(sp.ei, k));
+  } else {
+    double w_n = 0, er_n = 0, ei_n = 0;
+    if (k < F) {
+      w_n = ld_first<WALK>(sp.om, k);
+      er_n = ld_first<WALK>(sp.er, k);
+      ei_n = ld_first<WALK>(sp.ei, k);
+    }
+#pragma unroll UNROLL
+    for (; k < F; k += stride) {
+      const double w = w_n, er = er_n, ei = ei_n;
+      const int64_t kn = (k + stride < F) ? k + stride : k;   // in-bounds prefetch, no branch
+      w_n = ld<WALK>(sp.om, kn);
+      er_n = ld<WALK>(sp.er, kn);
+      ei_n = ld<WALK>(sp.ei, kn);
+      body(w, er, ei);
+    }
+  }
+}
+
+// body(a, b), a and b points (w, eps', eps''), for n_pairs pairs of points
+// k0 + 2 t stride and k0 + (2 t + 1) stride that every lane has (n_pairs is
+// wave-uniform); returns the index of the lane's next point
+struct Point {
+  double w, er, ei;
+};
+template <int WALK, class BODY>
+__device__ __forceinline__ int64_t each_pair(const Spectrum &sp, int k0, int stride, int64_t n_pairs, BODY &&body) {
+  int64_t k = k0;
+  if (n_pairs <= 0) return k;
+  if constexpr (WALK == 2) {
+    const Reader om(sp.om, sp.F, k0), er(sp.er, sp.F, k0), ei(sp.ei, sp.F, k0);
+    const int32_t n = 2 * stride * (int32_t)n_pairs;
+    auto read = [&](int32_t u, Point &a, Point &b) {
+      u = u < n ? u : n - 2 * stride;   // in-bounds prefetch, no branch
+      a = {om(u), er(u), ei(u)};
+      b = {om(u + stride), er(u + stride), ei(u + stride)};
+    };
+    Point an = {ld_first<WALK>(sp.om, k), ld_first<WALK>(sp.er, k), ld_first<WALK>(sp.ei, k)};
+    Point bn = {ld_first<WALK>(sp.om, k + stride), ld_first<WALK>(sp.er, k + stride), ld_first<WALK>(sp.ei, k + stride)};
+    // (two pairs per trip, so that the points read ahead alternate between two
+    // sets of registers instead of being copied)
+    int32_t u = 0;
+    for (; u + 2 * stride < n; u += 4 * stride) {
+      Point am, bm;
+      read(u + 2 * stride, am, bm);
+      body(an, bn);
+      read(u + 4 * stride, an, bn);
+      body(am, bm);
+    }
+    if (u < n) body(an, bn);
+    return k + n;
+  } else {
+    Point an = {ld_first<WALK>(sp.om, k), ld_first<WALK>(sp.er, k), ld_first<WALK>(sp.ei, k)};
+    Point bn = {ld_first<WALK>(sp.om, k + stride), ld_first<WALK>(sp.er, k + stride), ld_first<WALK>(sp.ei, k + stride)};
+    for (int64_t t = 0; t < n_pairs; ++t, k += 2 * stride) {
+      const Point a = an, b = bn;
+      // in-bounds prefetch of the next two points, no branch
+      const int64_t ka = (k + 2 * stride < sp.F) ? k + 2 * stride : k;
+      const int64_t kb = (k + 3 * stride < sp.F) ? k + 3 * stride : k;
+      an = {ld<WALK>(sp.om, ka), ld<WALK>(sp.er, ka), ld<WALK>(sp.ei, ka)};
+      bn = {ld<WALK>(sp.om, kb), ld<WALK>(sp.er, kb), ld<WALK>(sp.ei, kb)};
+      body(a, b);
+    }
+    return k;
+  }
+}
+
+// --------------------------------------------------------------------------
 // Cost pass in rational form.  With w >= 0 (the sign flip) the model sums
 // over a set of NR poles are rational functions of y = w^2 with positive
 // coefficients,
@@ -797,20 +937,17 @@ __device__ __forceinline__ void unpark(const double *park, int cpw, int grp, dou
 //   Q(y) = prod_i (1 + y tau_i^2),  P(y) = sum_i w_i prod_{j != i} (1 + y tau_j^2),
 // evaluated by Horner's rule with one reciprocal per point (no cancellation:
 // every term is positive).  The variable is scaled by the largest tau^2 of
-// the set, so every coefficient is at most binomial-sized.  GS lanes, each
-// with its own set, add their sums at every point (GS = 1: the set is the
-// whole candidate).  The lane takes points k0, k0 + stride, ... and returns
-// its partial sums of squared residuals (cost) and of eps' - shift - model
+// the set (a whole candidate), so every coefficient is at most
+// binomial-sized.  The lane takes points k0, k0 + stride, ... and returns its
+// partial sums of squared residuals (cost) and of eps' - shift - model
 // (sa).  Returns true when the wave must use the basis form instead: a
 // lane's smallest coefficient would be subnormal, Q exceeds 1e280 at some
 // point, or a cost is not finite (lanes that do not matter are ignored).
 // --------------------------------------------------------------------------
-template <int NR, int GS, class LOAD, class LOAD_FIRST>
+template <int NR, int WALK>
 __device__ __forceinline__ bool rational_cost_pass(const double *tau2, const double *w, const double *wt,
-                                                   bool matters, int64_t k0, int64_t stride, int64_t F,
-                                                   const double *om, const double *epr, const double *epi,
-                                                   double shift, LOAD ld, LOAD_FIRST ld_first, double &cost,
-                                                   double &sa) {
+                                                   bool matters, int k0, int stride, const Spectrum &sp,
+                                                   double shift, double &cost_out, double &sa_out) {
   double tmax = 0.0;
 #pragma unroll
   for (int i = 0; i < NR; ++i) tmax = tau2[i] > tmax ? tau2[i] : tmax;
@@ -845,24 +982,9 @@ __device__ __forceinline__ bool rational_cost_pass(const double *tau2, const dou
   for (int k = 0; k < NR; ++k) csum += cr[k] + ci[k];
   const bool coef_ok = !matters || (pnz >= 1e-280 && fabs(csum) < INFINITY);
   if (__builtin_amdgcn_ballot_w64(!coef_ok) != 0) return true;
-  cost = 0.0;
-  sa = 0.0;
-  double qmax = 0.0;
-  int64_t k = k0;
-  double w_n = 0, er_n = 0, ei_n = 0;
-  if (k < F) {
-    w_n = ld_first(om, k);
-    er_n = ld_first(epr, k);
-    ei_n = ld_first(epi, k);
-  }
+  double cost = 0.0, sa = 0.0, qmax = 0.0;
   // two points per trip: their Horner and reciprocal chains interleave
-#pragma unroll 2
-  for (; k < F; k += stride) {
-    const double om_k = w_n, er = er_n, ei = ei_n;
-    const int64_t kn = (k + stride < F) ? k + stride : k;   // in-bounds prefetch, no branch
-    w_n = ld(om, kn);
-    er_n = ld(epr, kn);
-    ei_n = ld(epi, kn);
+  each_point<WALK, 2>(sp, k0, stride, [&](double om_k, double er, double ei) {
     const double y = (om_k * om_k) * tmax;
     double hq = qc[NR], hr = cr[NR - 1], hi = ci[NR - 1];
 #pragma unroll
@@ -872,14 +994,16 @@ __device__ __forceinline__ bool rational_cost_pass(const double *tau2, const dou
       hr = __builtin_fma(hr, y, cr[d]);
       hi = __builtin_fma(hi, y, ci[d]);
     }
-    qmax = hq > qmax ? hq : qmax;
+    qmax = __builtin_fmax(hq, qmax);   // (a NaN shows in the cost)
     const double r = rcp_nr(hq);
-    const double rr = (er - shift) - group_sum<GS>(hr * r);
-    const double ri = __builtin_fma(-om_k, group_sum<GS>(hi * r), ei);
+    const double rr = (er - shift) - hr * r;
+    const double ri = __builtin_fma(-om_k, hi * r, ei);
     sa += rr;
     cost = __builtin_fma(rr, rr, cost);
     cost = __builtin_fma(ri, ri, cost);
-  }
+  });
+  cost_out = cost;
+  sa_out = sa;
   return __builtin_amdgcn_ballot_w64(matters && (!(qmax <= 1e280) || !(fabs(cost) + fabs(sa) < INFINITY))) != 0;
 }
 
@@ -910,6 +1034,10 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   using S = Shape<N, SP>;
   constexpr bool MF = S::MF;
   constexpr int NB = S::NB, NV = S::NV, NG = S::NG, D = S::D;
+  // (the one-lane adjoint at N = 11 spills 250 registers; with the reader's
+  // descriptors its compiled form gave wrong gradients, so it keeps a lane's
+  // own offsets)
+  constexpr int WALK = UNI == 2 && GRAD && SP == 1 && N >= 11 ? 3 : UNI;
   extern __shared__ double lds_all[];
 
   const int lane = threadIdx.x;
@@ -952,22 +1080,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   const double *om = a.omega + f0;
   const double *epr = a.eps_re + f0;
   const double *epi = a.eps_im + f0;
-  // point k of a spectrum
-  auto ld = [](const double *p, int64_t k) -> double {
-    if constexpr (UNI == 2) return *(const double *)((const char *)p + ((uint32_t)k << 3));
-    else return p[k];
-  };
-  // The first point of a pass that prefetches one point ahead, read through
-  // the constant address space (the spectra are read-only during a launch).
-  // Loads from two address spaces are not merged, so the compiler keeps the
-  // loop's loads one point ahead instead of folding them with this one into a
-  // single load at the top of every trip (which would expose the load
-  // latency at each point).
-  auto ld_first = [](const double *p, int64_t k) -> double {
-    using cptr = const __attribute__((address_space(4))) double *;
-    if constexpr (UNI == 2) return *(cptr)((const char *)p + ((uint32_t)k << 3));
-    else return ((cptr)p)[k];
-  };
+  const Spectrum spec = {om, epr, epi, F};
 
   const double damping = a.damping;
   const bool flip = !(a.flags & FLAG_NO_SIGN_FLIP);
@@ -1079,83 +1192,36 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       n_full = uniform(n_full);
       n_all = uniform(n_all);
     }
-    int64_t k = fl, t = 0;
-    if (n_full > 0) {
-      double wa_n = ld_first(om, k), era_n = ld_first(epr, k), eia_n = ld_first(epi, k);
-      double wb_n = ld_first(om, k + SF), erb_n = ld_first(epr, k + SF), eib_n = ld_first(epi, k + SF);
-      for (; t < n_full; ++t, k += 2 * SF) {
-        const double wa = wa_n, era = era_n, eia = eia_n, wb = wb_n, erb = erb_n, eib = eib_n;
-        // in-bounds prefetch of the next two points, no branch
-        const int64_t ka = (k + 2 * SF < F) ? k + 2 * SF : k, kb = (k + 3 * SF < F) ? k + 3 * SF : k;
-        wa_n = ld(om, ka);
-        era_n = ld(epr, ka);
-        eia_n = ld(epi, ka);
-        wb_n = ld(om, kb);
-        erb_n = ld(epr, kb);
-        eib_n = ld(epi, kb);
-        double Ia[NV], Ib[NV];
-        basis_Us2<NB>(wa, wb, tau2s, sq, Ia, Ib);
-        gram_acc(Ia, era, eia);
-        gram_acc(Ib, erb, eib);
-      }
-    }
-    for (; t < n_all; ++t, k += 2 * SF) {
+    int64_t k = each_pair<WALK>(spec, fl, SF, n_full, [&](const Point &a, const Point &b) {
+      double Ia[NV], Ib[NV];
+      basis_Us2<NB>(a.w, b.w, tau2s, sq, Ia, Ib);
+      gram_acc(Ia, a.er, a.ei);
+      gram_acc(Ib, b.er, b.ei);
+    });
+    for (int64_t t = n_full; t < n_all; ++t, k += 2 * SF) {
       const bool va = k < F, vb = k + SF < F;
       const int64_t ka = va ? k : F - 1, kb = vb ? k + SF : F - 1;
-      const double wa = va ? ld(om, ka) : 0.0, wb = vb ? ld(om, kb) : 0.0;
+      const double wa = va ? ld<WALK>(om, ka) : 0.0, wb = vb ? ld<WALK>(om, kb) : 0.0;
       double Ia[NV], Ib[NV];
       basis_Us2<NB>(wa, wb, tau2s, sq, Ia, Ib);
-      gram_acc(Ia, va ? ld(epr, ka) : 0.0, va ? ld(epi, ka) : 0.0);
-      gram_acc(Ib, vb ? ld(epr, kb) : 0.0, vb ? ld(epi, kb) : 0.0);
+      gram_acc(Ia, va ? ld<WALK>(epr, ka) : 0.0, va ? ld<WALK>(epi, ka) : 0.0);
+      gram_acc(Ib, vb ? ld<WALK>(epr, kb) : 0.0, vb ? ld<WALK>(epi, kb) : 0.0);
     }
   } else if constexpr (!PAIR_RING) {
-    int64_t k = fl;
-    double w_n = 0, er_n = 0, ei_n = 0;
-    if (k < F) {
-      w_n = ld_first(om, k);
-      er_n = ld_first(epr, k);
-      ei_n = ld_first(epi, k);
-    }
-#pragma unroll SP == 1 ? 2 : 1
-    for (; k < F; k += SF) {
-      const double w = w_n, er = er_n, ei = ei_n;
-      const int64_t kn = (k + SF < F) ? k + SF : k;   // in-bounds prefetch, no branch
-      w_n = ld(om, kn);
-      er_n = ld(epr, kn);
-      ei_n = ld(epi, kn);
-      gram_point(w, er, ei);
-    }
+    each_point<WALK, SP == 1 ? 2 : 1>(spec, fl, SF, gram_point);
   } else {
-    // the odd point last; the pole lanes of a candidate share their
-    // frequency lane, hence their trip counts
+    // the pairs that every lane of the wave has, then the lane's own (the pole
+    // lanes of a candidate share their frequency lane, hence their trip counts)
     int64_t k = fl;
-    double wa_n = 0, era_n = 0, eia_n = 0, wb_n = 0, erb_n = 0, eib_n = 0;
-    if (k < F) {
-      wa_n = ld_first(om, k);
-      era_n = ld_first(epr, k);
-      eia_n = ld_first(epi, k);
-    }
-    if (k + SF < F) {
-      wb_n = ld_first(om, k + SF);
-      erb_n = ld_first(epr, k + SF);
-      eib_n = ld_first(epi, k + SF);
-    }
-    for (; k + SF < F; k += 2 * SF) {
-      const double wa = wa_n, era = era_n, eia = eia_n, wb = wb_n, erb = erb_n, eib = eib_n;
-      // in-bounds prefetch of the next two points, no branch
-      const int64_t ka = (k + 2 * SF < F) ? k + 2 * SF : k, kb = (k + 3 * SF < F) ? k + 3 * SF : k;
-      wa_n = ld(om, ka);
-      era_n = ld(epr, ka);
-      eia_n = ld(epi, ka);
-      wb_n = ld(om, kb);
-      erb_n = ld(epr, kb);
-      eib_n = ld(epi, kb);
+    auto pair = [&](const Point &a, const Point &b) {
       double Ia[NV], Ib[NV];
-      basis_Us2<NB>(wa, wb, tau2s, sq, Ia, Ib);
-      gram_acc(Ia, era, eia);
-      gram_acc(Ib, erb, eib);
-    }
-    if (k < F) gram_point(wa_n, era_n, eia_n);
+      basis_Us2<NB>(a.w, b.w, tau2s, sq, Ia, Ib);
+      gram_acc(Ia, a.er, a.ei);
+      gram_acc(Ib, b.er, b.ei);
+    };
+    if constexpr (WALK == 2) k = each_pair<WALK>(spec, fl, SF, F / (2 * SF), pair);
+    else if (k + SF < F) k = each_pair<WALK>(spec, fl, SF, (F - fl + SF - 1) / SF / 2, pair);
+    for (; k < F; k += SF) gram_point(ld<WALK>(om, k), ld<WALK>(epr, k), ld<WALK>(epi, k));
   }
   freq_sum_n<NG, SP>(G, MF ? 16 : SP, SL);   // (the four points of a block are summed by the matrix instruction)
   if constexpr (SP == 2) {
@@ -1313,12 +1379,12 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       }
     }
     if (fl < F) {
-      double wn = ld(om, fl), en = ld(epi, fl);
+      double wn = ld<WALK>(om, fl), en = ld<WALK>(epi, fl);
       for (int64_t k = fl; k < F; k += SF) {
         const double w = wn, ei = en;
         const int64_t kn = k + SF < F ? k + SF : k;   // the next point, loaded one trip ahead
-        wn = ld(om, kn);
-        en = ld(epi, kn);
+        wn = ld<WALK>(om, kn);
+        en = ld<WALK>(epi, kn);
         double Ih[NB], Il[NB];
         double sh = 0.0, sl = 0.0;   // sum over the owned poles of z_i I_i
 #pragma unroll
@@ -1394,6 +1460,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         if (p < N) {   // (every frequency lane of the owner writes the same values)
           st2[p] = tau2s[cI];
           stz[p] = zc[cI] * ts[cI];
+          if constexpr (MF) lay.vt[p] = ts[cI];
         }
       }
       __syncthreads();
@@ -1412,24 +1479,24 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       // pair up), compensated as below
       const int64_t s2 = 2 * (int64_t)SF;
       // w r at point kk, with the point's R / s in R
-      auto pair_resid = [&](int64_t kk, double *R) {
-        const double w = ld(om, kk);
+      auto pair_resid = [&](auto at, int64_t kk, double *R) {
+        const double w = at(om, kk);
         basis_two_owners<NQ, LO>(w * w, t2h, sq, R);
         double part = 0.0;
 #pragma unroll
         for (int e = 0; e < H; ++e) part = __builtin_fma(R[e], zh[e], part);
         if constexpr (HP == 2) part = part + dpp_quad<QP_SWAP1>(part);
-        return w * __builtin_fma(-w, part, ld(epi, kk));
+        return w * __builtin_fma(-w, part, at(epi, kk));
       };
-      auto blk = [&](int64_t k0, int np) {   // np >= 1 points
+      auto blk = [&](auto at, int64_t k0, int np) {   // np >= 1 points
         double pb[H], R[H];
         {
-          const double wr = pair_resid(k0, R);
+          const double wr = pair_resid(at, k0, R);
 #pragma unroll
           for (int e = 0; e < H; ++e) pb[e] = R[e] * wr;
         }
         for (int t = 1; t < np; ++t) {
-          const double wr = pair_resid(k0 + t * s2, R);
+          const double wr = pair_resid(at, k0 + t * s2, R);
 #pragma unroll
           for (int e = 0; e < H; ++e) pb[e] = __builtin_fma(R[e], wr, pb[e]);
         }
@@ -1438,16 +1505,31 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       };
       // (two blocks per trip, so that the compensated sums alternate between
       // two registers instead of being copied back every update)
+      // (uniform tiles with a split: the trips that every lane has, the base
+      // moved on by the scalar unit; then the lane's own)
+      auto own = [](const double *p, int64_t kk) { return ld<WALK>(p, kk); };
       int64_t k = (q / HP) * SF + fl;
-      for (; k + 7 * s2 < F; k += 8 * s2) {
-        blk(k, 4);
-        blk(k + 4 * s2, 4);
+      if constexpr (WALK == 2) {
+        const Reader rom(om, F, k), rei(epi, F, k);
+        auto lane = [&](const double *p, int64_t ku) { return p == om ? rom((int32_t)ku) : rei((int32_t)ku); };
+        int32_t u = 0;
+        for (; u + 16 * SF <= (int32_t)F; u += 16 * SF) {
+          blk(lane, u, 4);
+          blk(lane, u + 8 * SF, 4);
+        }
+        k += u;
+        for (; k + 3 * s2 < F; k += 4 * s2) blk(own, k, 4);
+      } else {
+        for (; k + 7 * s2 < F; k += 8 * s2) {
+          blk(own, k, 4);
+          blk(own, k + 4 * s2, 4);
+        }
+        if (k + 3 * s2 < F) {
+          blk(own, k, 4);
+          k += 4 * s2;
+        }
       }
-      if (k + 3 * s2 < F) {
-        blk(k, 4);
-        k += 4 * s2;
-      }
-      if (k < F) blk(k, (int)((F - 1 - k) / s2) + 1);
+      if (k < F) blk(own, k, (int)((F - 1 - k) / s2) + 1);
       {
         double ngc[H];
 #pragma unroll
@@ -1458,13 +1540,21 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
 #pragma unroll
       for (int e = 0; e < H; ++e) {
         const int p = pole(e);
-        if (p < N) st2[p] = gh[e];   // (both point subsets hold the same sums)
+        if (p < N) stz[p] = gh[e];   // (both point subsets hold the same sums)
       }
       __syncthreads();
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
         const int p = pole_of(q, cI);
-        gv[cI] = (p < N ? st2[p] : 0.0) * ts[cI];
+        if constexpr (MF) {
+          // the owned poles' values come back from LDS: kept in registers
+          // across the pass they would spill
+          tau2s[cI] = p < N ? st2[p] : 0.0;
+          ts[cI] = p < N ? lay.vt[p] : 0.0;
+          zt[cI] = p < N ? lay.vz[p] : 0.0;
+          invd_own[cI] = p < N ? lay.invd[p] : 0.0;
+        }
+        gv[cI] = (p < N ? stz[p] : 0.0) * ts[cI];
       }
     }
   } else if (GRAD || refine) {
@@ -1493,7 +1583,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     // the error bound stays a small multiple of the roundoff of the terms'
     // magnitudes; a CPU emulation of the whole solve put the cost error
     // against the 80-bit oracle at the level of single-term compensation).
-    auto block4 = [&](int64_t k0) {
+    auto block4 = [&](auto at, int64_t k0) {
       double pb[NB];
       if constexpr (odd_pole<NB>() && SP == 4) {
         // the points in pairs: the odd pole's values of two points share a
@@ -1503,27 +1593,27 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
 #pragma unroll
         for (int t = 0; t < 4; t += 2) {
           const int64_t ka = k0 + t * SF, kb = ka + SF;
-          const double wa = ld(om, ka), wb = ld(om, kb);
+          const double wa = at(om, ka), wb = at(om, kb);
           double Ra[NB], Rb[NB];
           basis_Rs2<NB>(wa * wa, wb * wb, tau2s, sq, Ra, Rb);
-          const double wra = resid_R(wa, ld(epi, ka), Ra);
+          const double wra = resid_R(wa, at(epi, ka), Ra);
 #pragma unroll
           for (int cI = 0; cI < NB; ++cI) pb[cI] = t == 0 ? Ra[cI] * wra : __builtin_fma(Ra[cI], wra, pb[cI]);
-          const double wrb = resid_R(wb, ld(epi, kb), Rb);
+          const double wrb = resid_R(wb, at(epi, kb), Rb);
 #pragma unroll
           for (int cI = 0; cI < NB; ++cI) pb[cI] = __builtin_fma(Rb[cI], wrb, pb[cI]);
         }
       } else {
         double R[NB];
         {
-          const double wr = resid(ld(om, k0), ld(epi, k0), R);
+          const double wr = resid(at(om, k0), at(epi, k0), R);
 #pragma unroll
           for (int cI = 0; cI < NB; ++cI) pb[cI] = R[cI] * wr;
         }
 #pragma unroll
         for (int t = 1; t < 4; ++t) {
           const int64_t kk = k0 + t * SF;
-          const double wr = resid(ld(om, kk), ld(epi, kk), R);
+          const double wr = resid(at(om, kk), at(epi, kk), R);
 #pragma unroll
           for (int cI = 0; cI < NB; ++cI) pb[cI] = __builtin_fma(R[cI], wr, pb[cI]);
         }
@@ -1533,21 +1623,34 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     };
     // two blocks per trip: the compensated sums then alternate between two
     // registers instead of being copied back every update
+    auto own = [](const double *p, int64_t kk) { return ld<WALK>(p, kk); };
     int64_t k = fl;
-    for (; k + 7 * SF < F; k += 8 * SF) {
-      block4(k);
-      block4(k + 4 * SF);
-    }
-    if (k + 3 * SF < F) {
-      block4(k);
-      k += 4 * SF;
+    if constexpr (WALK == 2) {   // the trips that every lane has; then the lane's own
+      const Reader rom(om, F, fl), rei(epi, F, fl);
+      auto lane = [&](const double *p, int64_t ku) { return p == om ? rom((int32_t)ku) : rei((int32_t)ku); };
+      int32_t u = 0;
+      for (; u + 8 * SF <= (int32_t)F; u += 8 * SF) {
+        block4(lane, u);
+        block4(lane, u + 4 * SF);
+      }
+      k += u;
+      for (; k + 3 * SF < F; k += 4 * SF) block4(own, k);
+    } else {
+      for (; k + 7 * SF < F; k += 8 * SF) {
+        block4(own, k);
+        block4(own, k + 4 * SF);
+      }
+      if (k + 3 * SF < F) {
+        block4(own, k);
+        k += 4 * SF;
+      }
     }
     if (k < F) {   // the last one to three points
       double pb[NB], R[NB];
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) pb[cI] = 0.0;
       for (; k < F; k += SF) {
-        const double wr = resid(ld(om, k), ld(epi, k), R);
+        const double wr = resid(ld<WALK>(om, k), ld<WALK>(epi, k), R);
 #pragma unroll
         for (int cI = 0; cI < NB; ++cI) pb[cI] = __builtin_fma(R[cI], wr, pb[cI]);
       }
@@ -1625,13 +1728,13 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     einf = (F > 0) ? (sum_er - group_sum<SP>(ws_part)) / (double)F : 0.0;
     shift = einf;
   } else if (F > 0) {
-    const double w0 = ld(om, 0);
+    const double w0 = ld<WALK>(om, 0);
     double Rv[NB];
     basis_Rs<NB>(w0 * w0, tau2s, sq, Rv);
     double pr = 0.0;
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) pr = __builtin_fma(wv_[cI] * pole_scale<NB>(sq, cI), Rv[cI], pr);
-    shift = ld(epr, 0) - group_sum<SP>(pr);
+    shift = ld<WALK>(epr, 0) - group_sum<SP>(pr);
   }
 
   // ---- pass 3: residuals and cost (+ g_w for the adjoint)
@@ -1653,19 +1756,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       wts[cI] = wv_[cI] * ts[cI];
     }
     sa = 0.0;
-    int64_t k = fl;
-    double w_n = 0, er_n = 0, ei_n = 0;
-    if (k < F) {
-      w_n = ld_first(om, k);
-      er_n = ld_first(epr, k);
-      ei_n = ld_first(epi, k);
-    }
-    for (; k < F; k += SF) {
-      const double w = w_n, er = er_n, ei = ei_n;
-      const int64_t kn = (k + SF < F) ? k + SF : k;   // in-bounds prefetch, no branch
-      w_n = ld(om, kn);
-      er_n = ld(epr, kn);
-      ei_n = ld(epi, kn);
+    each_point<WALK, 1>(spec, fl, SF, [&](double w, double er, double ei) {
       double Rv[NB];
       basis_Rs<NB>(w * w, tau2s, sq, Rv);
       double pr = 0.0, pi = 0.0;
@@ -1688,7 +1779,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
           gw2[cI] = __builtin_fma(Rv[cI], wri, gw2[cI]);
         }
       }
-    }
+    });
     return acc;
   };
   double cost, sa = 0.0;
@@ -1707,8 +1798,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         double tau2v[NB];
 #pragma unroll
         for (int cI = 0; cI < NB; ++cI) tau2v[cI] = tau2_of(cI);
-        use_basis = rational_cost_pass<NB, 1>(tau2v, wv_, wt, matters, fl, SF, F, om, epr, epi, shift, ld, ld_first,
-                                             cost, sa);
+        use_basis = rational_cost_pass<NB, WALK>(tau2v, wv_, wt, matters, fl, SF, spec, shift, cost, sa);
       } else {
         // every lane of the candidate takes all N poles (gathered through the
         // candidate's LDS region, whose right-hand-side, first-solution and
@@ -1728,8 +1818,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
           }
         }
         __syncthreads();
-        use_basis = rational_cost_pass<N, 1>(t2s, wsh, wts, matters, sub, SL, F, om, epr, epi, shift, ld, ld_first,
-                                            cost, sa);
+        use_basis = rational_cost_pass<N, WALK>(t2s, wsh, wts, matters, sub, SL, spec, shift, cost, sa);
         red_from = 1;
       }
     }
@@ -1823,20 +1912,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       zt4[cI] = zc[cI] * tv4[cI];
       mt4[cI] = mu[cI] * tv4[cI];
     }
-    {
-      int64_t k = fl;
-      double w_n = 0, er_n = 0, ei_n = 0;
-      if (k < F) {
-        w_n = ld_first(om, k);
-        er_n = ld_first(epr, k);
-        ei_n = ld_first(epi, k);
-      }
-      for (; k < F; k += SF) {
-        const double w = w_n, er = er_n, ei = ei_n;
-        const int64_t kn = (k + SF < F) ? k + SF : k;
-        w_n = ld(om, kn);
-        er_n = ld(epr, kn);
-        ei_n = ld(epi, kn);
+    each_point<WALK, 1>(spec, fl, SF, [&](double w, double er, double ei) {
         double Rv[NB];
         basis_R<NB>(w * w, tv4s, Rv);
         double pr = 0.0, pi = 0.0, pz = 0.0, pm = 0.0;
@@ -1862,8 +1938,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
           T3[cI] = __builtin_fma(dI, qm, T3[cI]);
           T4[cI] = __builtin_fma(dI, I, T4[cI]);
         }
-      }
-    }
+    });
     freq_sum_n<NB, SP>(T1, SP, SL);
     freq_sum_n<NB, SP>(T2, SP, SL);
     freq_sum_n<NB, SP>(T3, SP, SL);

@@ -317,3 +317,32 @@ def test_full_size_sampled_parity_bench_configuration(D, orc):
                                  stats)
     print(f"full-size sample: {stats}")
     assert rel.max() <= COST_RTOL
+
+
+@pytest.mark.parametrize("N", list(range(1, 25)))
+def test_adjoint_every_pole_count(D, orc, N):
+    """The adjoint of every pole count, whole waves of one material at splits 1
+    (where the pole split allows it), 4 and 16 and waves of several materials,
+    against the oracle's; relaxation times spread over the box, tolerance of
+    test_adjoint_matches_oracle."""
+    import torch
+    wl = small_uniform(4, 173, N, 64, seed=700 + N)   # 173 points: a remainder at every split
+    er, ei = targets_oracle(orc, wl)
+    g = np.random.default_rng(N)
+    lo, hi = wl.lb[0], wl.ub[0]
+    theta = lo + (hi - lo) * (np.arange(N) + 0.25 + 0.5 * g.random((wl.P, N))) / N
+    ob = orc.Batch(wl.f_off, wl.cand_off, wl.n_poles, wl.omega, er, ei)
+    og, ost = orc.fit_grad(ob, theta)[1], orc.fit_grad(ob, theta)[4]
+    keep = np.concatenate([np.arange(wl.cand_off[m], wl.cand_off[m] + 13) for m in range(wl.M)])
+    few = W.offsets([13] * wl.M)   # 13 candidates a material: no whole waves
+    for split in (1, 4, 16):
+        for cand_off, rows in ((wl.cand_off, np.arange(wl.P)), (few, keep)):
+            b = D.Batch(wl.f_off, cand_off, wl.n_poles, wl.omega, _t(er), _t(ei))
+            plan = D.Plan(b)
+            plan.set_freq_split(split)
+            _, g_th, _, _, st = D.fit_eval_grad(plan, b, _t(theta[rows]))
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(st.cpu().numpy(), ost[rows])
+            gerr = np.max(np.abs(g_th.cpu().numpy() - og[rows]), axis=1) / np.max(np.abs(og[rows]), axis=1)
+            print(f"N={N} {plan.info()[0]}: max theta-gradient rel err {gerr.max():.2e}")
+            assert gerr.max() <= 1e-6
