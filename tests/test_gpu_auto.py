@@ -68,3 +68,35 @@ def test_fit_auto_matches_oracle(D, orc):
         np.testing.assert_allclose(gth[m, :n], oth[m, :n], rtol=1e-5, atol=1e-6)
         np.testing.assert_allclose(gw[m, :n], ow[m, :n], rtol=1e-4, atol=1e-6 * np.max(np.abs(ow[m, :n])))
         assert np.all(np.isnan(gth[m, n:]))
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 23, 24])
+def test_afe_block_forms(D, N):
+    """The error of one candidate a block: few candidates (four wavefronts
+    each) and many (one each), odd and even pole counts, spectra around the
+    points a block takes at once (256 and 1,024), several materials without
+    candidates; and relaxation times beyond the admissible range, whose loss
+    terms vanish.  Against the sums in numpy; tolerance of
+    test_afe_matches_oracle."""
+    g = np.random.default_rng(N)
+    for Fm, per in (([1, 63, 257, 1025], [3, 0, 2, 1]), ([255, 256], [1100, 1000])):
+        om = np.concatenate([W.log_grid(1e6, 1e10, max(f, 2))[:f] for f in Fm])
+        f_off, c_off = W.offsets(Fm), W.offsets(per)
+        er, ei = 2 + g.random(len(om)), g.random(len(om))
+        ei[::7] = 0.0
+        P = int(c_off[-1])
+        th = -12 + 5 * g.random((P, N))
+        th[P - 1] = 200.0   # w tau = 1e207: x^2 overflows, the basis is 0
+        w, e = g.random((P, N)), 1 + g.random(P)
+        b = D.Batch(f_off, c_off, np.full(len(Fm), N), om, _t(er), _t(ei))
+        got = D.afe(b, _t(th), _t(w), _t(e)).cpu().numpy()
+        for c in (0, 1, 2, P // 2, P - 1):
+            m = int(np.searchsorted(c_off, c, side="right") - 1)
+            s = slice(f_off[m], f_off[m + 1])
+            with np.errstate(over="ignore"):
+                x = om[s, None] * 10.0 ** th[c]
+                R = 1 / (1 + x * x)
+            dr, di = np.abs(er[s] - e[c] - R @ w[c]), np.abs(ei[s] - (x * R) @ w[c])
+            nz = ei[s] != 0
+            ref = 100 * (np.mean(dr / er[s]) + (np.mean(di[nz] / ei[s][nz]) if nz.any() else 0.0))
+            assert got[c] == pytest.approx(ref, rel=1e-12), (c, m)
