@@ -406,3 +406,18 @@ def test_split_below_four_lanes_runs_as_split_four(D, orc, N):
         for x, y in zip(out[split], out[4]):
             assert torch.equal(torch.nan_to_num(x), torch.nan_to_num(y)), split
     _check_eval(D, orc, wl, theta, split=1, tag=f"narrow N{N}")
+
+
+@pytest.mark.parametrize("F", [1, 255, 1023, 1024, 1025, 3000])
+def test_basis_chunks(D, orc, F):
+    """The materialised basis at the edges of a block's points (1,024, four a
+    thread), rows longer than the pole count; tolerance of
+    test_basis_matches_oracle."""
+    import torch
+    om = W.log_grid(1e5, 1e11, max(F, 2))[:F]
+    theta = np.random.default_rng(F).uniform(-12.5, -6.0, (3, 4))
+    re, im = D.basis(torch.tensor(om, device="cuda"), torch.tensor(theta, device="cuda"), 3)
+    for c in range(3):
+        r0, i0 = orc.basis(om, theta[c, :3])
+        np.testing.assert_allclose(re[c].cpu().numpy(), r0, rtol=1e-15, atol=0)
+        np.testing.assert_allclose(im[c].cpu().numpy(), i0, rtol=1e-15, atol=0)
