@@ -157,7 +157,7 @@ int debye_plan_destroy(debye_plan *plan);
 /* Override the schedule's frequency split (lanes per candidate along the
  * frequency axis, a power of two; 0 restores the automatic choice) for pole
  * count n_poles (0 = all). Used by the autotuner and the tests.  Pole counts
- * split over four lanes (17 and more) keep at least four frequency lanes in the
+ * split over four lanes (15 and more) keep at least four frequency lanes in the
  * kernel: a narrower split sets their tiles, each run as several waves, with
  * the results of split 4.  Re-tiling
  * (here or in debye_plan_autotune) makes the plan's next optimiser run

@@ -34,7 +34,7 @@
 // neighbour by DPP quad permutes.  Padded poles get tau = 0, so their loss
 // column is exactly zero and they drop out.
 //
-// Gram matrix on the four-lane split (SP = 4, N >= 17): 4x4 tiles of poles on
+// Gram matrix on the four-lane split (SP = 4, N >= 15): 4x4 tiles of poles on
 // the matrix cores, v_mfma_f64_4x4x4 (four blocks; D += A B per block, K = 4
 // points).  Its lanes are numbered pole (bits 0-1), block (bits 2-3), point
 // (bits 4-5) in A and in B alike, so a lane that forms the basis of poles
@@ -50,10 +50,11 @@
 // every lane, forward evaluation of N = 20 on one box: F = 4096 (32,768
 // candidates) 3.06 -> 2.69 ms, F = 200 (131,072) 1.18 -> 0.87 ms, F = 50 0.92
 // -> 0.58 ms; N = 17 at F = 4096 3.00 -> 2.71 ms, N = 24 3.88 -> 3.35 ms; the
-// adjoint at N = 20, F = 4096, 6.00 -> 5.45 ms.  At N = 12 to 16 the padding
-// to whole tiles and the smaller reciprocal groups of a lane cost more than
-// the ring's moves (F = 2000: N = 12 1.49 ms on the ring, 1.71 on tiles; N = 16
-// 2.12 and 2.15).
+// adjoint at N = 20, F = 4096, 6.00 -> 5.45 ms; N = 16 (65,536 candidates of F =
+// 2000) 2.08 -> 1.96 ms, (131,072 of F = 200) 0.80 -> 0.63 ms.  At N = 12 to 14
+// the padding to whole tiles and the smaller reciprocal groups of a lane cost
+// what the ring's moves do, or more (F = 2000: N = 12 1.45 ms on the ring, 1.46
+// on tiles; N = 13 1.74 and 1.93).
 
 #pragma once
 
@@ -2007,9 +2008,13 @@ void fit_dd_kernel(const FitArgs a) {
 // pole count alone, autotuned frequency split): one lane per candidate up to
 // N = 11 (at N = 9..11 its register spills cost less than the DPP traffic and
 // the padded pole of the two-lane ring; at N = 12 they do not), two lanes up
-// to N = 16, four above, with the Gram matrix on the matrix cores (figures at
-// the top of the file).
-constexpr int pole_split_for(int n) { return n <= 11 ? 1 : (n <= 16 ? 2 : 4); }
+// to N = 14, four above, with the Gram matrix on the matrix cores (figures at
+// the top of the file; N = 14 at F = 2000 1.80 ms on two lanes, 1.95 on four).
+// The adjoint keeps two lanes up to N = 16: its third and fourth passes take
+// four pole sums a point, which four lanes combine in two steps each (N = 16,
+// F = 2000: 3.97 ms on two lanes, 4.22 on four).
+constexpr int pole_split_for(int n) { return n <= 11 ? 1 : (n <= 14 ? 2 : 4); }
+constexpr int pole_split_grad(int n) { return n <= 11 ? 1 : (n <= 16 ? 2 : 4); }
 
 // Blocks of a cost-kernel grid: eight times the longest of the 8 XCD tile
 // lists (block b runs tile b / 8 of XCD b % 8's list).
@@ -2024,13 +2029,15 @@ inline unsigned fit_grid_blocks(const FitArgs &a) {
 // loads; wider splits: per-lane offsets) or the general one.  The grid covers
 // the longest of the 8 XCD tile lists.
 template <int N, bool GRAD> hipError_t launch_fit_variant(const FitArgs &a, int64_t n_tiles, bool uni, hipStream_t s) {
-  constexpr int SP = pole_split_for(N);
+  constexpr int SP = GRAD ? pole_split_grad(N) : pole_split_for(N);
   const size_t lds = (size_t)Shape<N, SP>::LDS_DOUBLES * 8 * a.cand_per_wave;
   FitArgs b = a;
   b.n_tiles = n_tiles;
+  // (the plan's tiles are the forward kernel's: as many lanes a candidate)
+  b.freq_split = a.freq_split * (pole_split_for(N) / SP);
   const unsigned blocks = fit_grid_blocks(a);
   if (blocks == 0) return hipSuccess;
-  if (uni && a.freq_split == 1) {
+  if (uni && b.freq_split == 1) {
     if constexpr (!Shape<N, SP>::MF)
       hipLaunchKernelGGL((fit_kernel<N, SP, GRAD, 1>), dim3(blocks), dim3(64), lds, s, b);
   } else if (uni)
