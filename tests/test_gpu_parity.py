@@ -421,3 +421,34 @@ def test_basis_chunks(D, orc, F):
         r0, i0 = orc.basis(om, theta[c, :3])
         np.testing.assert_allclose(re[c].cpu().numpy(), r0, rtol=1e-15, atol=0)
         np.testing.assert_allclose(im[c].cpu().numpy(), i0, rtol=1e-15, atol=0)
+
+
+@pytest.mark.parametrize("F", [1, 63, 64, 257])
+def test_material_ranges(D, orc, F):
+    """Every kind at the edges of a wave and a block, several materials in one,
+    and parameters outside the fast functions' ranges (alpha above 1, a
+    relaxation time far out of the band, beta = 3), Jacobian included;
+    tolerances of test_material_targets_match_oracle."""
+    hn = [W.hn_params(3.0, 20.0, t, a, b) for t, a, b in
+          ((1e-9, 0.7, 0.5), (1e-9, 1.2, 0.5), (1e-160, 0.6, 0.9), (1e-9, 0.5, 3.0), (1e-9, 1.0, 1.0))]
+    jon, crim = np.zeros(16), np.zeros(16)
+    jon[:4], crim[:5] = [4.0, 9.0, 1e8, 0.3], [4.9, 75.0, 9.2e-12, 0.2, 6.0]
+    tab = np.zeros(16)
+    tab[:10], tab[14] = [3.0, 2, 20.0, 1e-9, 0.7, 0.5, 9.0, 1e-10, 1.0, 0.4], 0.01
+    kind = np.array([1, 1, 1, 1, 0, 2, 3, 4, 5, 6], np.int8)
+    params = np.stack(hn + [hn[0], hn[0], jon, crim, tab])
+    sizes = [F, 3, 1, F, 5, F, 2, F, 7, F]
+    f_off = W.offsets(sizes)
+    om = np.concatenate([W.log_grid(1e6, 1e10, max(f, 2))[:f] for f in sizes])
+    oer, oei, oJ = orc.material_eval(kind, params, f_off, om, noise_seed=9, jac=True)
+    er, ei, J = D.material_eval(kind, params, f_off, om, noise_seed=9, jac=True)
+    e2, i2 = D.material_eval(kind, params, f_off, om, noise_seed=9)
+    for a, b in ((er, oer), (ei, oei), (e2, oer), (i2, oei)):
+        np.testing.assert_allclose(a.cpu().numpy(), b, rtol=2e-13, atol=1e-13)
+    J = J.cpu().numpy()
+    np.testing.assert_array_equal(np.isnan(J), np.isnan(oJ))
+    for m in range(len(kind)):
+        s = slice(f_off[m], f_off[m + 1])
+        if not np.isnan(oJ[s]).any():
+            scale = np.abs(oJ[s]).max(axis=(0, 2))
+            assert np.all(np.abs(J[s] - oJ[s]).max(axis=(0, 2)) <= 1e-12 * scale), m
