@@ -356,6 +356,7 @@ dfit::FitArgs fit_args(const debye_plan *p, const Bucket &bk, const debye_batch 
   a.flags = flags;
   a.freq_split = bk.lane_sf;
   a.cand_per_wave = bk.cpw;
+  a.short_spectra = bk.work <= dfit::SHORT_SPECTRA * bk.n_cands * bk.N;
   a.lane_cand = bk.d_lane_cand;
   a.lane_mat = bk.d_lane_mat;
   for (int x = 0; x < 9; ++x) a.xcd_off[x] = bk.xcd_off[x];

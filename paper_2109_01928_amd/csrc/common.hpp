@@ -38,8 +38,9 @@ __device__ __forceinline__ double rsq_nr(double d) {
 }
 
 // Cross-lane move of a double inside a quad (DPP quad_perm; CTRL encodes the
-// source lane of each of the four lanes, two bits per lane).
-// Every source lane of a quad permutation is valid, so the move needs no
+// source lane of each of the four lanes, two bits per lane), or by another DPP
+// control that moves whole rows.
+// Every source lane of these is valid, so the move needs no
 // "old" value (bound_ctrl set) and compiles to two bare v_mov_b32_dpp.
 template <int CTRL> __device__ __forceinline__ double dpp_quad(double v) {
   int lo = __builtin_amdgcn_mov_dpp((int)__double2loint(v), CTRL, 0xF, 0xF, true);
@@ -47,7 +48,9 @@ template <int CTRL> __device__ __forceinline__ double dpp_quad(double v) {
   return __hiloint2double(hi, lo);
 }
 constexpr int QP_SWAP1 = 0xB1;  // [1,0,3,2]: lane ^ 1
-constexpr int QP_ROT1 = 0x39;   // [1,2,3,0]: (lane + 1) mod 4
-constexpr int QP_SWAP2 = 0x4E;  // [2,3,0,1]: lane ^ 2 = (lane + 2) mod 4
+constexpr int QP_REV = 0x1B;    // [3,2,1,0]: lane ^ 3
+constexpr int QP_SWAP2 = 0x4E;  // [2,3,0,1]: lane ^ 2
+constexpr int ROW_HALF_MIRROR = 0x141;   // lane ^ 7
+constexpr int ROW_ROR8 = 0x128;          // rotation of a row of 16 lanes by 8: lane ^ 8
 
 }  // namespace dfit

@@ -10,6 +10,8 @@ struct debye_batch;
 
 namespace dfit {
 
+constexpr int64_t SHORT_SPECTRA = 768;
+
 // Arguments of the cost / adjoint kernel (one work tile per 64-lane block).
 struct FitArgs {
   const int64_t *f_off;
@@ -20,6 +22,7 @@ struct FitArgs {
   uint32_t flags;
   int32_t freq_split;     // SF: lanes per candidate along the frequency axis
   int32_t cand_per_wave;  // 64 / (SP * SF)
+  bool short_spectra;     // SHORT_SPECTRA points or fewer on average
   int64_t n_tiles;        // work tiles (one per wavefront)
   // tiles of XCD x are xcd_off[x] .. xcd_off[x+1]-1 (in the order to run them)
   int64_t xcd_off[9];

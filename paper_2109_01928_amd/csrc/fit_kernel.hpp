@@ -58,10 +58,15 @@
 
 #pragma once
 
+#include <type_traits>
+
 #include "common.hpp"
 #include "fit_eval.hpp"
 
 namespace dfit {
+
+using lds_ptr = __attribute__((address_space(3))) double *;
+using lds_cptr = const __attribute__((address_space(3))) double *;
 
 template <int N, int SP> struct Shape {
   static_assert(SP == 1 || SP == 2 || SP == 4, "pole split must be 1, 2 or 4");
@@ -79,6 +84,13 @@ template <int N, int SP> struct Shape {
 
 constexpr __host__ __device__ int tri(int n, int i, int j) { return i * n - (i * (i - 1)) / 2 + (j - i); }
 
+// Orders a wave's LDS accesses across its lanes: the LDS serves one wave's
+// accesses in order, so only the compiler has to keep it.
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
 // the neighbour's value on the two-lane ring
 __device__ __forceinline__ double ring_fetch(double v) { return dpp_quad<QP_SWAP1>(v); }
 
@@ -87,9 +99,49 @@ __device__ __forceinline__ double ring_fetch(double v) { return dpp_quad<QP_SWAP
 // lanes are numbered as the matrix instruction has them (pole lane in bits
 // 0-1, block in bits 2-3, point in bits 4-5) and a candidate's lanes by pole
 // lane, point, block
-template <int SP> __device__ __forceinline__ int lane_mask(int m) {
-  if constexpr (SP == 4) return m < 4 ? m : m < 16 ? m << 2 : m >> 2;
-  else return m;
+template <int SP> constexpr int lane_mask(int m) { return SP == 4 ? (m < 4 ? m : m < 16 ? m << 2 : m >> 2) : m; }
+
+// A lane's value and that of lane ^ MASK, as a pair whose order does not matter
+// (both lanes get the same two): by DPP inside a row of 16 lanes and by the
+// row and half swaps across rows, all in the vector unit.  Through the LDS
+// crossbar (ds_bpermute) each step of a butterfly waited for a round trip: the
+// sums after the Gram pass took 2,500 of an evaluation's 21,000 cycles for 40
+// candidates of 5 poles and 50 points at split 8.
+struct Two {
+  double a, b;
+};
+template <int MASK> __device__ __forceinline__ Two with_lane_xor(double v) {
+  if constexpr (MASK == 1) {
+    return {v, dpp_quad<QP_SWAP1>(v)};
+  } else if constexpr (MASK == 2) {
+    return {v, dpp_quad<QP_SWAP2>(v)};
+  } else if constexpr (MASK == 4) {
+    return {v, dpp_quad<QP_REV>(dpp_quad<ROW_HALF_MIRROR>(v))};   // lane ^ 7 ^ 3
+  } else if constexpr (MASK == 8) {
+    return {v, dpp_quad<ROW_ROR8>(v)};
+  } else {
+    const uint32_t lo = (uint32_t)__double2loint(v), hi = (uint32_t)__double2hiint(v);
+    if constexpr (MASK == 16) {
+      const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+      const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+      return {__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1])};
+    } else {
+      const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+      const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+      return {__hiloint2double((int)h[0], (int)l[0]), __hiloint2double((int)h[1], (int)l[1])};
+    }
+  }
+}
+
+// step(mask) for the bits FROM .. s_lanes / 2 of a lane's index among its
+// candidate's lanes
+template <int SP, int FROM, class STEP> __device__ __forceinline__ void each_bit(int s_lanes, STEP &&step) {
+  if constexpr (FROM < WAVE) {
+    if (FROM < s_lanes) {
+      step(std::integral_constant<int, lane_mask<SP>(FROM)>());
+      each_bit<SP, FROM * 2>(s_lanes, step);
+    }
+  }
 }
 
 // sum over the SP lanes of a candidate (bit-identical in all of them)
@@ -104,31 +156,20 @@ template <int SP> __device__ __forceinline__ double group_sum(double v) {
   }
 }
 
-// sum over the SF frequency lanes of a candidate (xor butterfly over bits
-// from .. s_lanes / 2 of the lane's index among its candidate's lanes)
-template <int SP> __device__ __forceinline__ double freq_sum(double v, int from, int s_lanes) {
-  for (int m = from; m < s_lanes; m <<= 1) v += __shfl_xor(v, lane_mask<SP>(m), WAVE);
-  return v;
-}
-
-// freq_sum of K values at once.  Each step's exchanges go through the LDS
-// crossbar; issued eight at a time, they wait for it once per eight values
-// instead of once per value (value by value, the additions and so the
-// results are those of freq_sum).
-template <int K, int SP> __device__ __forceinline__ void freq_sum_n(double *v, int from, int s_lanes) {
-  for (int m = from; m < s_lanes; m <<= 1) {
-    const int lm = lane_mask<SP>(m);
+// sums over the SF frequency lanes of a candidate (xor butterfly over the bits
+// from FROM on; all lanes end with the same bits)
+template <int K, int SP, int FROM> __device__ __forceinline__ void freq_sum_n(double *v, int s_lanes) {
+  each_bit<SP, FROM>(s_lanes, [&](auto mask) {
 #pragma unroll
-    for (int e0 = 0; e0 < K; e0 += 8) {
-      double o[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (e0 + e < K) o[e] = __shfl_xor(v[e0 + e], lm, WAVE);
-#pragma unroll
-      for (int e = 0; e < 8; ++e)
-        if (e0 + e < K) v[e0 + e] += o[e];
+    for (int e = 0; e < K; ++e) {
+      const Two t = with_lane_xor<decltype(mask)::value>(v[e]);
+      v[e] = t.a + t.b;
     }
-  }
+  });
+}
+template <int SP, int FROM> __device__ __forceinline__ double freq_sum(double v, int s_lanes) {
+  freq_sum_n<1, SP, FROM>(&v, s_lanes);
+  return v;
 }
 
 // Compensated accumulation sum += a * b (Kahan's summation with the running
@@ -142,32 +183,25 @@ __device__ __forceinline__ void kahan_fma_acc(double &sum, double &c, double a, 
   sum = t;
 }
 
-// xor-butterfly of K double-doubles (hi[e] + lo_in[e]) over the SF frequency
-// lanes, the exchanges issued together as in freq_sum_n; hi[e] receives the
-// sum rounded to a double.  TwoSum's error term does not depend on the
-// operand order, so all lanes end with the same bits.
-template <int K, int SP>
-__device__ __forceinline__ void freq_sum_dd_n(double *hi, const double *lo_in, int from, int s_lanes) {
+// The same for K double-doubles (hi[e] + lo_in[e]); hi[e] receives the sum
+// rounded to a double.  TwoSum's error term does not depend on the operand
+// order, so all lanes end with the same bits.
+template <int K, int SP, int FROM>
+__device__ __forceinline__ void freq_sum_dd_n(double *hi, const double *lo_in, int s_lanes) {
   double lo[K];
 #pragma unroll
   for (int e = 0; e < K; ++e) lo[e] = lo_in[e];
-  for (int m = from; m < s_lanes; m <<= 1) {
-    const int lm = lane_mask<SP>(m);
-    double oh[K], ol[K];
+  each_bit<SP, FROM>(s_lanes, [&](auto mask) {
 #pragma unroll
     for (int e = 0; e < K; ++e) {
-      oh[e] = __shfl_xor(hi[e], lm, WAVE);
-      ol[e] = __shfl_xor(lo[e], lm, WAVE);
-    }
-#pragma unroll
-    for (int e = 0; e < K; ++e) {
-      const double s = hi[e] + oh[e];
-      const double bv = s - hi[e];
-      const double se = (hi[e] - (s - bv)) + (oh[e] - bv);
+      const Two h = with_lane_xor<decltype(mask)::value>(hi[e]), l = with_lane_xor<decltype(mask)::value>(lo[e]);
+      const double s = h.a + h.b;
+      const double bv = s - h.a;
+      const double se = (h.a - (s - bv)) + (h.b - bv);
       hi[e] = s;
-      lo[e] = (lo[e] + ol[e]) + se;
+      lo[e] = (l.a + l.b) + se;
     }
-  }
+  });
 #pragma unroll
   for (int e = 0; e < K; ++e) hi[e] = hi[e] + lo[e];
 }
@@ -318,6 +352,19 @@ template <int NB> struct Groups {
   static constexpr int NS = NQ > 0 ? NQ : 1;     // (array size)
 };
 
+// the largest k >= 0 of the wave (shifts and broadcasts over the rows of 16
+// lanes leave it in the last lane)
+__device__ __forceinline__ int wave_max(int k) {
+  auto step = [&](int o) { k = o > k ? o : k; };
+  step(__builtin_amdgcn_update_dpp(0, k, 0x111, 0xF, 0xF, false));   // row_shr:1
+  step(__builtin_amdgcn_update_dpp(0, k, 0x112, 0xF, 0xF, false));   // row_shr:2
+  step(__builtin_amdgcn_update_dpp(0, k, 0x114, 0xF, 0xF, false));   // row_shr:4
+  step(__builtin_amdgcn_update_dpp(0, k, 0x118, 0xF, 0xF, false));   // row_shr:8
+  step(__builtin_amdgcn_update_dpp(0, k, 0x142, 0xA, 0xF, false));   // row_bcast:15 into rows 1 and 3
+  step(__builtin_amdgcn_update_dpp(0, k, 0x143, 0xC, 0xF, false));   // row_bcast:31 into rows 2 and 3
+  return __builtin_amdgcn_readlane(k, WAVE - 1);
+}
+
 // scale s = 2^-k of each group (from tau^2 of its poles), the same in every
 // lane of the wave (all lanes call this together)
 template <int NB>
@@ -335,12 +382,7 @@ __device__ __forceinline__ void group_scales(const double *tau2, int *kq, double
     // rejected input (its results are discarded) from scaling its wave's
     // valid lanes out of range
     k = k < 253 ? k : 253;
-#pragma unroll
-    for (int m = 1; m < WAVE; m <<= 1) {
-      const int o = __shfl_xor(k, m, WAVE);
-      k = o > k ? o : k;
-    }
-    k = __builtin_amdgcn_readfirstlane(k);
+    k = wave_max(k);
     kq[g] = k;
     sq[g] = __hiloint2double((1023 - k) << 20, 0);   // 2^-k
   }
@@ -490,7 +532,7 @@ __device__ __forceinline__ bool equilibrate_factor(MAT &A, double *invd, double 
   for (int i = 0; i < N; ++i) {
     double g = A[tri(N, i, i)];
     ok = ok && (g > 0.0) && (g < INFINITY);
-    invd[i] = 1.0 / sqrt(g);
+    invd[i] = rsq_nr(g);
   }
 #pragma unroll
   for (int i = 0; i < N; ++i) {
@@ -504,10 +546,8 @@ __device__ __forceinline__ bool equilibrate_factor(MAT &A, double *invd, double 
 #pragma unroll
     for (int l = 0; l < j; ++l) s = __builtin_fma(-A[tri(N, l, j)], A[tri(N, l, j)], s);
     ok = ok && (s > tol);
-    double u = sqrt(s);
-    double ui = 1.0 / u;
+    const double ui = rsq_nr(s);   // (the pivot itself is never read)
     uinv[j] = ui;
-    A[tri(N, j, j)] = u;
 #pragma unroll
     for (int k = j + 1; k < N; ++k) {
       double t = A[tri(N, j, k)];
@@ -549,8 +589,6 @@ __device__ __forceinline__ void chol_solve(const MAT &A, const double *uinv, VEC
 // by four (their loads issued together, the additions in their order); the
 // backward solve is unrolled whole (all its addresses are constants).  The
 // operations and their order are those of the register form above.
-using lds_ptr = __attribute__((address_space(3))) double *;
-using lds_cptr = const __attribute__((address_space(3))) double *;
 
 constexpr __host__ __device__ int tcol(int i, int j) { return j * (j + 1) / 2 + i; }
 
@@ -563,7 +601,7 @@ __device__ __noinline__ bool lds_equilibrate_factor(lds_ptr A, lds_ptr invd, lds
   for (int i = 0; i < N; ++i) {
     const double g = A[tcol(i, i)];
     ok = ok && (g > 0.0) && (g < INFINITY);
-    dv[i] = 1.0 / sqrt(g);
+    dv[i] = rsq_nr(g);
     invd[i] = dv[i];
   }
 #pragma unroll
@@ -578,10 +616,8 @@ __device__ __noinline__ bool lds_equilibrate_factor(lds_ptr A, lds_ptr invd, lds
 #pragma unroll 4
     for (int l = 0; l < j; ++l) s = __builtin_fma(-cj[l], cj[l], s);
     ok = ok && (s > tol);
-    const double u = sqrt(s);
-    const double ui = 1.0 / u;
+    const double ui = rsq_nr(s);   // (the pivot itself is never read)
     uinv[j] = ui;
-    cj[j] = u;
     for (int k = j + 1; k < N; ++k) {
       const lds_ptr ck = A + tcol(0, k);
       double t = ck[j];
@@ -612,13 +648,6 @@ template <int N> __device__ __noinline__ void lds_chol_solve(lds_cptr A, lds_cpt
     xv[i] = s * uinv[i];
     x[i] = xv[i];
   }
-}
-
-// Orders a wave's LDS accesses across its lanes: the LDS serves one wave's
-// accesses in order, so only the compiler has to keep it.
-__device__ __forceinline__ void wave_sync() {
-  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-  __builtin_amdgcn_wave_barrier();
 }
 
 // The factorisation and the solves shared by 16 lanes of a candidate (the
@@ -660,13 +689,13 @@ template <int N> struct Coop {
     for (int i = 0; i < N0; ++i) c0[i] = A[tcol(0, k0) + i];
 #pragma unroll
     for (int i = 0; i < N1; ++i) c1[i] = A[tcol(0, k1) + i];
-    const double d0 = 1.0 / sqrt(A[tcol(k0, k0)]);
+    const double d0 = rsq_nr(A[tcol(k0, k0)]);
     invd[k0] = d0;
     x0 = b[k0] * d0;
     double d1 = 0.0;
     x1 = 0.0;
     if constexpr (N1 > 0) {
-      d1 = 1.0 / sqrt(A[tcol(k1, k1)]);
+      d1 = rsq_nr(A[tcol(k1, k1)]);
       invd[k1] = d1;
       x1 = b[k1] * d1;
     }
@@ -801,10 +830,11 @@ __device__ __forceinline__ void unpark(const double *park, int cpw, int grp, dou
 // --------------------------------------------------------------------------
 // How (WALK): 0, a lane's own 64-bit index; 1, the same, wave-uniform (split 1:
 // scalar loads); 2, a wave-uniform point and a lane's own constant offset; 3,
-// a lane's own 32-bit offset.
+// a lane's own 32-bit offset; 4, a lane's own index into LDS.
 // point k
 template <int WALK> __device__ __forceinline__ double ld(const double *p, int64_t k) {
-  if constexpr (WALK >= 2) return *(const double *)((const char *)p + ((uint32_t)k << 3));
+  if constexpr (WALK == 4) return ((lds_cptr)p)[k];
+  else if constexpr (WALK >= 2) return *(const double *)((const char *)p + ((uint32_t)k << 3));
   else return p[k];
 }
 // The first point of a pass that reads one point ahead, through the constant
@@ -814,7 +844,8 @@ template <int WALK> __device__ __forceinline__ double ld(const double *p, int64_
 // top of every trip (which would expose the load latency at each point).
 template <int WALK> __device__ __forceinline__ double ld_first(const double *p, int64_t k) {
   using cptr = const __attribute__((address_space(4))) double *;
-  if constexpr (WALK >= 2) return *(cptr)((const char *)p + ((uint32_t)k << 3));
+  if constexpr (WALK == 4) return ((lds_cptr)p)[k];
+  else if constexpr (WALK >= 2) return *(cptr)((const char *)p + ((uint32_t)k << 3));
   else return ((cptr)p)[k];
 }
 // Uniform tiles with a frequency split: the wave's lanes walk together, so a
@@ -1224,7 +1255,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     else if (k + SF < F) k = each_pair<WALK>(spec, fl, SF, (F - fl + SF - 1) / SF / 2, pair);
     for (; k < F; k += SF) gram_point(ld<WALK>(om, k), ld<WALK>(epr, k), ld<WALK>(epi, k));
   }
-  freq_sum_n<NG, SP>(G, MF ? 16 : SP, SL);   // (the four points of a block are summed by the matrix instruction)
+  freq_sum_n<NG, SP, MF ? 16 : SP>(G, SL);   // (the four points of a block are summed by the matrix instruction)
   if constexpr (SP == 2) {
     double tv[NV];
 #pragma unroll
@@ -1239,13 +1270,13 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
 #pragma unroll
       for (int j = i; j < N; ++j) G[tri(N, i, j)] *= ts[i] * ts[j];
   }
-  freq_sum_n<NB, SP>(bv, SP, SL);
+  freq_sum_n<NB, SP, SP>(bv, SL);
 #pragma unroll
   for (int cI = 0; cI < NB; ++cI) {
     bv[cI] = bv[cI] * ts[cI];
     bad = bad || !(fabs(bv[cI]) < INFINITY);
   }
-  sum_er = freq_sum<SP>(sum_er, SP, SL);
+  sum_er = freq_sum<SP, SP>(sum_er, SL);
   bad = bad || !(fabs(sum_er) < INFINITY);
   bad = group_sum<SP>(bad ? 1.0 : 0.0) != 0.0;
 
@@ -1276,7 +1307,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
 #pragma unroll
           for (int j = i; j < N; ++j) park[tri(N, i, j) * cpw + grp] = (i == j) ? uinv_r[i] : G[tri(N, i, j)];
       }
-      __syncthreads();
+      wave_sync();
     }
   } else {
     // assemble the packed triangle in LDS (all lanes of a candidate write the same values)
@@ -1295,7 +1326,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
           vb[p] = bv[cI];
         }
       }
-      __syncthreads();
+      wave_sync();
       const int row = lane >> 4;
 #pragma unroll
       for (int I = 0; I < NB; ++I) {
@@ -1322,7 +1353,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       }
       if (p1 < N) vb[p1] = bv[cI];
     }
-    __syncthreads();
+    wave_sync();
     if constexpr (MF) {
       const Coop<N> coop((lds_ptr)A, (lds_ptr)uinv, sub & 15, first_lane);
       double x0, x1;
@@ -1334,7 +1365,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       for (int i = 0; i < N; ++i) vz[i] = vb[i] * invd[i];
       lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vz);
     }
-    __syncthreads();
+    wave_sync();
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
       const int p = pole_of(q, cI);
@@ -1424,7 +1455,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         }
       }
     }
-    freq_sum_dd_n<NB, SP>(gv, gl, SP, SL);
+    freq_sum_dd_n<NB, SP, SP>(gv, gl, SL);
   } else if constexpr (!GRAD && (SP == 4 || (SP == 2 && NB <= 6))) {
     if (refine) {
       // The pole splits run this pass over pairs of owner lanes: lane q takes
@@ -1464,7 +1495,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
           if constexpr (MF) lay.vt[p] = ts[cI];
         }
       }
-      __syncthreads();
+      wave_sync();
       double t2h[H], zh[H];
 #pragma unroll
       for (int e = 0; e < H; ++e) {
@@ -1535,15 +1566,15 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         double ngc[H];
 #pragma unroll
         for (int e = 0; e < H; ++e) ngc[e] = -gc[e];
-        freq_sum_dd_n<H, SP>(gh, ngc, HP, SL);   // the point subsets and the frequency lanes
+        freq_sum_dd_n<H, SP, HP>(gh, ngc, SL);   // the point subsets and the frequency lanes
       }
-      __syncthreads();
+      wave_sync();
 #pragma unroll
       for (int e = 0; e < H; ++e) {
         const int p = pole(e);
         if (p < N) stz[p] = gh[e];   // (both point subsets hold the same sums)
       }
-      __syncthreads();
+      wave_sync();
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
         const int p = pole_of(q, cI);
@@ -1662,9 +1693,9 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       double ngl[NB];
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) ngl[cI] = -gl[cI];
-      freq_sum_dd_n<NB, SP>(gv, ngl, SP, SL);
+      freq_sum_dd_n<NB, SP, SP>(gv, ngl, SL);
     }
-    if constexpr (GRAD) freq_sum_n<NB, SP>(Sv, SP, SL);
+    if constexpr (GRAD) freq_sum_n<NB, SP, SP>(Sv, SL);
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
       gv[cI] = gv[cI] * ts[cI];
@@ -1691,7 +1722,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         const int p = pole_of(q, cI);
         if (p < N) vw[p] = __builtin_fma(gv[cI], invd_own[cI], -damping * zt[cI]);
       }
-      __syncthreads();
+      wave_sync();
       if constexpr (MF) {
         const Coop<N> coop((lds_ptr)A, (lds_ptr)uinv, sub & 15, first_lane);
         double x0, x1;
@@ -1702,7 +1733,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       } else {
         lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vw);
       }
-      __syncthreads();
+      wave_sync();
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
         const int p = pole_of(q, cI);
@@ -1808,7 +1839,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         // NB combined across lanes
         const LdsLayout<N> lay(L);
         double *t2s = lay.vb, *wsh = lay.vz, *wts = lay.invd;
-        __syncthreads();
+        wave_sync();
 #pragma unroll
         for (int cI = 0; cI < NB; ++cI) {
           const int p = pole_of(q, cI);
@@ -1818,7 +1849,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
             wts[p] = wt[cI];
           }
         }
-        __syncthreads();
+        wave_sync();
         use_basis = rational_cost_pass<N, WALK>(t2s, wsh, wts, matters, sub, SL, spec, shift, cost, sa);
         red_from = 1;
       }
@@ -1828,9 +1859,15 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       red_from = SP;
     }
   }
-  cost = freq_sum<SP>(cost, red_from, SL);
+  {
+    double part[2] = {cost, sa};
+    constexpr int K = GRAD ? 1 : 2;
+    if (SP > 1 && red_from == 1) freq_sum_n<K, SP, 1>(part, SL);
+    else freq_sum_n<K, SP, SP>(part, SL);
+    cost = part[0];
+    sa = part[1];
+  }
   if constexpr (!GRAD) {
-    sa = freq_sum<SP>(sa, red_from, SL);
     if (F > 0) {
       cost -= sa * (sa / (double)F);
       einf = shift + sa / (double)F;
@@ -1859,8 +1896,8 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     // ---- adjoint: mu = M^-1 (s o g_w), M = D A D
     if (a.grad_cost) gc = active ? a.grad_cost[c] : 0.0;
     double mt[NB], mu[NB];
-    freq_sum_n<NB, SP>(gw2, SP, SL);
-    freq_sum_n<NB, SP>(gw, SP, SL);
+    freq_sum_n<NB, SP, SP>(gw2, SL);
+    freq_sum_n<NB, SP, SP>(gw, SL);
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
       gw[cI] = -2.0 * pole_scale<NB>(sq, cI) * __builtin_fma(tau_of(cI), gw2[cI], gw[cI]);
@@ -1879,7 +1916,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
         const int p = pole_of(q, cI);
         if (p < N) vw[p] = mt[cI];
       }
-      __syncthreads();
+      wave_sync();
       if constexpr (MF) {
         const Coop<N> coop((lds_ptr)A, (lds_ptr)uinv, sub & 15, first_lane);
         double x0, x1;
@@ -1890,7 +1927,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
       } else {
         lds_chol_solve<N>((lds_cptr)A, (lds_cptr)uinv, (lds_ptr)vw);
       }
-      __syncthreads();
+      wave_sync();
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
         const int p = pole_of(q, cI);
@@ -1940,10 +1977,10 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
           T4[cI] = __builtin_fma(dI, I, T4[cI]);
         }
     });
-    freq_sum_n<NB, SP>(T1, SP, SL);
-    freq_sum_n<NB, SP>(T2, SP, SL);
-    freq_sum_n<NB, SP>(T3, SP, SL);
-    freq_sum_n<NB, SP>(T4, SP, SL);
+    freq_sum_n<NB, SP, SP>(T1, SL);
+    freq_sum_n<NB, SP, SP>(T2, SL);
+    freq_sum_n<NB, SP, SP>(T3, SL);
+    freq_sum_n<NB, SP, SP>(T4, SL);
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
       T1[cI] = LN10 * T1[cI];
@@ -2010,11 +2047,12 @@ void fit_dd_kernel(const FitArgs a) {
 // the padded pole of the two-lane ring; at N = 12 they do not), two lanes up
 // to N = 14, four above, with the Gram matrix on the matrix cores (figures at
 // the top of the file; N = 14 at F = 2000 1.80 ms on two lanes, 1.95 on four).
-// The adjoint keeps two lanes up to N = 16: its third and fourth passes take
-// four pole sums a point, which four lanes combine in two steps each (N = 16,
-// F = 2000: 3.97 ms on two lanes, 4.22 on four).
+// The adjoint of long spectra keeps two lanes up to N = 16: its third and fourth
+// passes take four pole sums a point, which four lanes combine in two steps
+// each (N = 16, F = 2000: 3.97 ms on two lanes, 4.22 on four); short ones are
+// bound by the solves, which four lanes share (F = 200: 1.20 and 1.05 ms).
 constexpr int pole_split_for(int n) { return n <= 11 ? 1 : (n <= 14 ? 2 : 4); }
-constexpr int pole_split_grad(int n) { return n <= 11 ? 1 : (n <= 16 ? 2 : 4); }
+constexpr int pole_split_long_grad(int n) { return n <= 11 ? 1 : (n <= 16 ? 2 : 4); }
 
 // Blocks of a cost-kernel grid: eight times the longest of the 8 XCD tile
 // lists (block b runs tile b / 8 of XCD b % 8's list).
@@ -2028,8 +2066,7 @@ inline unsigned fit_grid_blocks(const FitArgs &a) {
 // kernel, in the uniform-tile form the plan found (split 1: scalar spectrum
 // loads; wider splits: per-lane offsets) or the general one.  The grid covers
 // the longest of the 8 XCD tile lists.
-template <int N, bool GRAD> hipError_t launch_fit_variant(const FitArgs &a, int64_t n_tiles, bool uni, hipStream_t s) {
-  constexpr int SP = GRAD ? pole_split_grad(N) : pole_split_for(N);
+template <int N, int SP, bool GRAD> hipError_t launch_fit_split(const FitArgs &a, int64_t n_tiles, bool uni, hipStream_t s) {
   const size_t lds = (size_t)Shape<N, SP>::LDS_DOUBLES * 8 * a.cand_per_wave;
   FitArgs b = a;
   b.n_tiles = n_tiles;
@@ -2045,6 +2082,10 @@ template <int N, bool GRAD> hipError_t launch_fit_variant(const FitArgs &a, int6
   else
     hipLaunchKernelGGL((fit_kernel<N, SP, GRAD, 0>), dim3(blocks), dim3(64), lds, s, b);
   return hipGetLastError();
+}
+template <int N, bool GRAD> hipError_t launch_fit_variant(const FitArgs &a, int64_t n_tiles, bool uni, hipStream_t s) {
+  if (GRAD && !a.short_spectra) return launch_fit_split<N, pole_split_long_grad(N), GRAD>(a, n_tiles, uni, s);
+  return launch_fit_split<N, pole_split_for(N), GRAD>(a, n_tiles, uni, s);
 }
 
 // The forward kernel with the extended-precision refinement: the general
