@@ -440,9 +440,9 @@ int debye_fit_auto(const debye_batch *mats, const int64_t *f_off_host, const dou
  *                    NULL).  Generation 0 is the initial population: call it
  *                    with u = x and cost_u = cost(x).
  *   debye_de_run:    init, generation 0, then `iters` generations, each
- *                    [trial -> debye_fit_eval -> select]; with use_graph the
- *                    generation is captured once into a HIP graph and
- *                    replayed (bit-identical).  history needs
+ *                    [trial -> debye_fit_eval -> select]; with use_graph and
+ *                    more than 16 pole counts the generation is captured once
+ *                    into a HIP graph and replayed (bit-identical).  history needs
  *                    hist_ld >= iters + 1.  Calls with one plan must not overlap.
  * All pointers are device pointers; rows have stride ld >= max_poles.
  * ------------------------------------------------------------------------ */
@@ -500,8 +500,8 @@ int debye_de_run(const debye_plan *plan, const debye_batch *b, int64_t ld, const
  *   debye_da_accept: generation t >= 1 as above; t = 0 takes y = x with
  *                    cost_y = cost(x) (the initial chains).
  *   debye_da_run:    init, generation 0, `iters` generations [visit ->
- *                    debye_fit_eval -> accept], optionally replayed from a
- *                    captured HIP graph (bit-identical); hist_ld >= iters + 1.
+ *                    debye_fit_eval -> accept], replayed from a captured
+ *                    HIP graph as debye_de_run (bit-identical); hist_ld >= iters + 1.
  * Defaults of the method: qv = 2.62, qa = -5, t0 = 5230.
  * ------------------------------------------------------------------------ */
 typedef struct debye_da_params {

@@ -429,6 +429,21 @@ int graph_replay(SwarmGraph &g, const std::vector<unsigned char> &key, int32_t t
   return DEBYE_OK;
 }
 
+// Whether an optimiser's iterations are replayed from a captured graph: with
+// few launches an iteration, enqueueing them costs less than the replay (its
+// nodes follow one another about 4 us apart, and it adds the counter's).  Per
+// iteration, replayed and enqueued: 8 materials of 64 particles (N = 12, 200
+// points) 56 and 46 us, 64 of 64 (N = 10, 300 points) 50 and 42, 12 ragged
+// materials with 9 pole counts 160 and 148.
+// A stream under capture keeps the replay, which it refuses.
+bool capturing(hipStream_t s) {
+  hipStreamCaptureStatus st;
+  return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
+}
+bool replayed(const debye_plan *p, int32_t use_graph, hipStream_t s) {
+  return use_graph && (p->buckets.size() > 16 || capturing(s));
+}
+
 struct KeyBytes {
   std::vector<unsigned char> v;
   template <class T> void put(const T &x) {
@@ -1055,14 +1070,15 @@ int debye_pso_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const 
   debye_plan *plan = const_cast<debye_plan *>(pc);
   SwarmGraph &g = plan->graph;
   hipStream_t s = stream;
-  if (use_graph) {
+  const bool replay = replayed(plan, use_graph, stream);
+  if (replay) {
     if ((rc = graph_enter(g, stream))) return rc;
     s = g.stream;
   }
   dfit::PsoArgs a0 = pso_args(b, ld, lb, ub, p, 0, 0, sw);
   CHECK_HIP(dfit::launch_pso_init(a0, b->n_cand, s), "swarm init");
   if ((rc = debye_fit_eval(plan, b, sw->x, ld, damping, flags, sw->cost, nullptr, nullptr, sw->status, s))) return rc;
-  if (!use_graph) {
+  if (!replay) {
     for (int32_t t = 1; t <= iters; ++t) {
       CHECK_HIP(dfit::launch_pso_step(pso_args(b, ld, lb, ub, p, t, 1, sw), s), "swarm step");
       if ((rc = debye_fit_eval(plan, b, sw->x, ld, damping, flags, sw->cost, nullptr, nullptr, sw->status, s)))
@@ -1088,7 +1104,7 @@ int debye_pso_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const 
     if (rc) return rc;
   }
   CHECK_HIP(dfit::launch_pso_step(pso_args(b, ld, lb, ub, p, iters + 1, 0, sw), s), "final bests");
-  if (use_graph) return graph_leave(g, stream);
+  if (replay) return graph_leave(g, stream);
   return DEBYE_OK;
 }
 
@@ -1183,7 +1199,8 @@ int debye_de_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
   debye_plan *plan = const_cast<debye_plan *>(pc);
   SwarmGraph &g = plan->de_graph;
   hipStream_t s = stream;
-  if (use_graph) {
+  const bool replay = replayed(plan, use_graph, stream);
+  if (replay) {
     if ((rc = graph_enter(g, stream))) return rc;
     s = g.stream;
   }
@@ -1216,7 +1233,7 @@ int debye_de_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
     CHECK_HIP(dfit::launch_de_select(a, gs), "DE select");
     return DEBYE_OK;
   };
-  if (!use_graph) {
+  if (!replay) {
     for (int32_t t = 1; t <= iters; ++t)
       if ((rc = generation(s, t, nullptr))) return rc;
     return DEBYE_OK;
@@ -1326,7 +1343,8 @@ int debye_da_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
   debye_plan *plan = const_cast<debye_plan *>(pc);
   SwarmGraph &g = plan->da_graph;
   hipStream_t s = stream;
-  if (use_graph) {
+  const bool replay = replayed(plan, use_graph, stream);
+  if (replay) {
     if ((rc = graph_enter(g, stream))) return rc;
     s = g.stream;
   }
@@ -1358,7 +1376,7 @@ int debye_da_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
     CHECK_HIP(dfit::launch_da_accept(a, gs), "annealing accept");
     return DEBYE_OK;
   };
-  if (!use_graph) {
+  if (!replay) {
     for (int32_t t = 1; t <= iters; ++t)
       if ((rc = generation(s, t, nullptr))) return rc;
     return DEBYE_OK;
