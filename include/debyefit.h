@@ -346,11 +346,16 @@ int debye_pso_step(const debye_batch *b, int64_t ld, const double *lb, const dou
 /* ------------------------------------------------------------------------
  * A whole swarm fit: pso_init, cost evaluation, then `iters` x (pso_step with
  * move, cost evaluation), then a bests-only pso_step; P*(iters+1) evaluations
- * per material.  With use_graph != 0 one iteration (step -> evaluation ->
- * iteration-counter increment) is captured once as a HIP graph (kept in the
- * plan and reused while the arguments are unchanged) and replayed `iters`
- * times on a stream owned by the plan, ordered after and before `stream` by
- * events; results are bit-identical to use_graph = 0.  history needs
+ * per material.  A small fit (at most 1,024 wavefronts an evaluation, 4 a
+ * material, N <= 11, the swarm's state and spectrum within a block's LDS, no
+ * DEBYE_FLAG_DD_REFINE) runs as one launch per pole count, a block a material.
+ * Otherwise, with use_graph != 0 and more than 16 pole counts, one iteration
+ * (step -> evaluation -> iteration-counter increment) is captured once as a
+ * HIP graph (kept in the plan and reused while the arguments are unchanged) and
+ * replayed `iters` times on a stream owned by the plan, ordered after and before
+ * `stream` by events; fewer launches an iteration cost less enqueued one by one.
+ * Results are bit-identical either way.  With use_graph != 0 the stream must
+ * not be under capture.  history needs
  * hist_ld >= iters + 1.  Calls with one plan must not overlap.
  * ------------------------------------------------------------------------ */
 typedef struct debye_swarm {

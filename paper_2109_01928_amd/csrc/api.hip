@@ -128,10 +128,19 @@ int pick_split(const debye_plan &p, const Bucket &b) {
   auto tuned = p.sf_tuned.find(b.N);
   if (tuned != p.sf_tuned.end()) return std::min(tuned->second, max_sf);
   // smallest power of two that gives TARGET_WAVES waves, without splitting
-  // short spectra below 16 points per lane
+  // short spectra below 16 points per lane, or 12 where the swarms then still
+  // have a wave for each SIMD of one CU (a block runs such a swarm whole: 40
+  // particles of 5 poles and 50 points 11.6 us an iteration at split 4, 15.1 at 2,
+  // 12.8 at 8, whose fifth wave shares a SIMD)
   const int64_t avg_f = b.n_cands ? b.work / (b.n_cands * b.N) : 1;
+  int64_t most = 0;   // candidates of the largest swarm
+  for (int32_t m : b.mats) most = std::max(most, p.cand_off[m + 1] - p.cand_off[m]);
   int sf = min_split(b.SP);
-  while (sf < max_sf && (b.n_cands * b.SP * sf + 63) / 64 < TARGET_WAVES && avg_f / (2 * sf) >= 16) sf *= 2;
+  auto wider = [&]() {
+    const int64_t points = avg_f / (2 * sf);
+    return points >= 16 || (points >= 12 && most * b.SP * 2 * sf <= 256);
+  };
+  while (sf < max_sf && (b.n_cands * b.SP * sf + 63) / 64 < TARGET_WAVES && wider()) sf *= 2;
   // the SP > 1 path keeps each candidate's normal matrix in LDS: fewer
   // candidates per wave until two waves per SIMD fit
   const int lds = dfit::lds_bytes_per_candidate(b.N);
@@ -922,6 +931,48 @@ int fit_eval_grad_external(const debye_plan *p, const debye_batch *b, const doub
 }
 }  // namespace dfit
 
+namespace {
+// A swarm fit whose batch cannot fill the chip is bound by its launches: up to
+// SWARM_TILES wavefronts an evaluation (one for every SIMD) it runs as one
+// launch, a block a material (swarm.hip), where the block's wavefronts, one a
+// SIMD, take all of the material's tiles at once.  One-lane candidates only (N
+// <= 11): the tiles of several lanes keep too much in LDS for a swarm's state
+// to join them.  Per iteration, in one launch and step by step, 64 particles, F
+// = 100: 8 materials of 5 poles 17.5 and 24.0 us, of 11 poles 31.9 and 43.7;
+// 250 materials 19.3 and 25.7, 35.6 and 59.8; past the limit, 500 materials of
+// 8 poles 46.0 and 43.6.  With eight wavefronts a block (F = 200, 5 poles) it
+// would lose: 26.1 and 24.3.
+constexpr int64_t SWARM_TILES = 1024;
+
+// wavefronts of a block for the materials of bucket bk (0: step by step) and
+// the LDS of the largest one's state
+int swarm_waves(const debye_plan &p, const Bucket &bk, int64_t *state) {
+  int64_t most = 0;
+  *state = 0;
+  if (bk.N > dfit::SWARM_POLES) return 0;
+  for (int32_t m : bk.mats) {
+    const int64_t P = p.cand_off[m + 1] - p.cand_off[m], F = p.f_off[m + 1] - p.f_off[m];
+    if (P > INT16_MAX || F > INT16_MAX) return 0;   // (their state is far beyond the LDS)
+    most = std::max(most, (P + bk.cpw - 1) / bk.cpw);
+    *state = std::max(*state, dfit::swarm_state_bytes(P, bk.N, F));
+  }
+  const int64_t per_wave = std::max<int64_t>(1, (int64_t)dfit::lds_bytes_per_candidate(bk.N) * bk.cpw);
+  return most <= dfit::SWARM_WAVES && most * per_wave + *state <= dfit::SWARM_LDS ? (int)most : 0;
+}
+
+bool swarm_in_one_launch(const debye_plan &p, uint32_t flags) {
+  if (p.launch != DEBYE_LAUNCH_BUCKETS || (flags & DEBYE_FLAG_DD_REFINE)) return false;
+  int64_t tiles = 0, state;
+  for (const Bucket &bk : p.buckets) tiles += bk.n_tiles;
+  if (tiles == 0 || tiles > SWARM_TILES) return false;
+  for (int32_t m = 0; m < p.M; ++m)
+    if (p.cand_off[m + 1] == p.cand_off[m]) return false;   // a swarm without particles
+  for (const Bucket &bk : p.buckets)
+    if (swarm_waves(p, bk, &state) == 0) return false;
+  return true;
+}
+}  // namespace
+
 extern "C" {
 
 int debye_fit_eval_grad(const debye_plan *p, const debye_batch *b, const double *log10_tau, int64_t ld,
@@ -1068,6 +1119,18 @@ int debye_pso_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const 
   if (iters < 0) return fail(DEBYE_ERANGE, "iters must be >= 0");
   if (sw->history && sw->hist_ld < (int64_t)iters + 1) return fail(DEBYE_ERANGE, "hist_ld must be >= iters + 1");
   debye_plan *plan = const_cast<debye_plan *>(pc);
+  if (swarm_in_one_launch(*plan, flags) && !(use_graph && capturing(stream)))
+    return for_buckets(plan, stream, [&](const Bucket &bk, hipStream_t bs) -> int {
+      dfit::FitArgs fa = fit_args(plan, bk, b, sw->x, ld, damping, flags);
+      fa.cost = sw->cost;
+      fa.status = sw->status;
+      int64_t state;
+      const int waves = swarm_waves(*plan, bk, &state);
+      CHECK_HIP(dfit::launch_swarm(bk.N, fa, pso_args(b, ld, lb, ub, p, 0, 1, sw), bk.d_mats, (int32_t)bk.mats.size(),
+                                   waves, (int32_t)state, iters, bs),
+                "swarm launch");
+      return DEBYE_OK;
+    });
   SwarmGraph &g = plan->graph;
   hipStream_t s = stream;
   const bool replay = replayed(plan, use_graph, stream);

@@ -109,6 +109,15 @@ struct PsoArgs {
   double *history;
   int64_t hist_ld;
 };
+// A whole swarm fit of the materials in `mats` (all with n poles) in one launch
+// (swarm.hip): blocks of `waves` wavefronts, one block a material, with
+// state_bytes of LDS for the largest one's state beside the waves' regions.
+constexpr int SWARM_POLES = 11;               // at most
+constexpr int SWARM_WAVES = 4;                // at most: one per SIMD of a CU
+constexpr int64_t SWARM_LDS = 158 * 1024;     // dynamic LDS of a block (of 160 KiB)
+int64_t swarm_state_bytes(int64_t P, int N, int64_t F);
+hipError_t launch_swarm(int n, const FitArgs &fit, const PsoArgs &a, const int32_t *mats, int32_t n_mats, int32_t waves,
+                        int32_t state_bytes, int32_t iters, hipStream_t s);
 hipError_t launch_pso_init(const PsoArgs &a, int64_t n_cand, hipStream_t s);
 hipError_t launch_pso_step(const PsoArgs &a, hipStream_t s);
 hipError_t launch_set_counter(int32_t *c, int32_t value, hipStream_t s);

@@ -1060,8 +1060,18 @@ template <int N, int SP, bool GRAD, int UNI> constexpr int waves_per_simd() {
 // XR: the refinement pass in double-double (FLAG_DD_REFINE; forward only).
 // One work tile (one wavefront: the candidates the plan lists for it) of the
 // cost kernel for N poles; the kernels below call it for their tiles.
-template <int N, int SP, bool GRAD, int UNI, bool XR = false>
-__device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
+// OWN: a tile of candidates 0 .. n-1 of a material in their order, by one wave
+// of a block of several, outside the plan's lists; relaxation times ([n][N]
+// log10 tau), spectra and costs in LDS.
+struct OwnTile {
+  int tid;
+  double *lds;   // the wave's region
+  int32_t n, F;
+  const double *theta, *om, *er, *ei;
+  double *cost;
+};
+template <int N, int SP, bool GRAD, int UNI, bool XR = false, bool OWN = false>
+__device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile, const OwnTile own = OwnTile()) {
   static_assert(!(XR && GRAD), "the extended-precision refinement is a forward-kernel form");
   using S = Shape<N, SP>;
   constexpr bool MF = S::MF;
@@ -1069,10 +1079,11 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   // (the one-lane adjoint at N = 11 spills 250 registers; with the reader's
   // descriptors its compiled form gave wrong gradients, so it keeps a lane's
   // own offsets)
-  constexpr int WALK = UNI == 2 && GRAD && SP == 1 && N >= 11 ? 3 : UNI;
-  extern __shared__ double lds_all[];
+  constexpr int WALK = OWN ? 4 : UNI == 2 && GRAD && SP == 1 && N >= 11 ? 3 : UNI;
+  extern __shared__ double lds_block[];
+  double *const lds_all = OWN ? own.lds : lds_block;
 
-  const int lane = threadIdx.x;
+  const int lane = OWN ? own.tid & (WAVE - 1) : threadIdx.x;
   const int SF = UNI == 1 ? 1 : a.freq_split;
   const int SL = SP * SF;            // lanes per candidate
   // candidate slot in the wave, the lane's index among the candidate's lanes,
@@ -1088,11 +1099,11 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   // (lane q holds row or column q of every tile of four poles)
   auto pole_of = [](int own, int cI) -> int { return MF ? 4 * cI + own : own * NB + cI; };
   const int64_t slot = tile * a.cand_per_wave + grp;
-  const int32_t cand = a.lane_cand[slot];
+  const int64_t cand = !OWN ? (int64_t)a.lane_cand[slot] : slot < own.n ? slot : -1;
   const bool active = cand >= 0;
   // (inactive lanes of the four-lane split take the first slot's spectrum, so
   // that their wave's point counts are those of its candidates)
-  const int32_t mat = active ? a.lane_mat[slot] : MF ? a.lane_mat[tile * a.cand_per_wave] : 0;
+  const int32_t mat = OWN ? 0 : active ? a.lane_mat[slot] : MF ? a.lane_mat[tile * a.cand_per_wave] : 0;
   const int64_t c = active ? cand : 0;
   // a wave whose candidates all belong to materials marked done exits
   // before any work (wave-uniform: a block is one wave)
@@ -1101,7 +1112,9 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   if (a.skip_mat && __builtin_amdgcn_ballot_w64(active && a.skip_mat[mat] == 0) == 0) return;
 
   int64_t f0 = 0, F = 0;
-  if constexpr (UNI != 0) {
+  if constexpr (OWN) {
+    F = own.F;
+  } else if constexpr (UNI != 0) {
     const int32_t mu = __builtin_amdgcn_readfirstlane(a.lane_mat[tile * a.cand_per_wave]);
     f0 = a.f_off[mu];
     F = a.f_off[mu + 1] - f0;
@@ -1109,9 +1122,9 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     f0 = a.f_off[mat];
     F = a.f_off[mat + 1] - f0;
   }
-  const double *om = a.omega + f0;
-  const double *epr = a.eps_re + f0;
-  const double *epi = a.eps_im + f0;
+  const double *om = OWN ? own.om : a.omega + f0;
+  const double *epr = OWN ? own.er : a.eps_re + f0;
+  const double *epi = OWN ? own.ei : a.eps_im + f0;
   const Spectrum spec = {om, epr, epi, F};
 
   const double damping = a.damping;
@@ -1125,7 +1138,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
     const int p = pole_of(q, cI);
     tau[cI] = 0.0;
     if (p < N && active) {
-      const double t = a.theta[c * a.ld + p];
+      const double t = OWN ? ((lds_cptr)own.theta)[c * N + p] : a.theta[c * a.ld + p];
       bad = bad || !(fabs(t) <= THETA_LIMIT);
       tau[cI] = exp10(t);
     }
@@ -1879,11 +1892,17 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile) {
   const bool writer = active && fl == 0;
   double gc = 1.0;
   if (writer && q == 0) {
-    a.cost[c] = st == ST_OK ? cost : (st == ST_SINGULAR ? INFINITY : NAN);
+    const double result = st == ST_OK ? cost : (st == ST_SINGULAR ? INFINITY : NAN);
+    if constexpr (OWN) {
+      ((lds_ptr)own.cost)[c] = result;
+      if (a.status) a.status[c] = (int8_t)st;
+      return;
+    }
+    a.cost[c] = result;
     if (a.eps_inf) a.eps_inf[c] = st == ST_OK ? einf : NAN;
     if (a.status) a.status[c] = (int8_t)st;
   }
-  if (writer && a.weights) {
+  if (!OWN && writer && a.weights) {
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) {
       const int p = pole_of(q, cI);

@@ -8,8 +8,7 @@
 #include <algorithm>
 
 #include "common.hpp"
-#include "rng.hpp"
-#include "fit_eval.hpp"
+#include "pso.hpp"
 
 namespace dfit {
 
@@ -35,9 +34,8 @@ __global__ __launch_bounds__(256) void pso_init_kernel(const PsoArgs a, int64_t 
   const int N = a.n_poles[m];
   const double lo = a.lb[m], span = __dsub_rn(a.ub[m], a.lb[m]);
   for (int d = 0; d < N; ++d) {
-    const U64x4 r = philox4x64((uint64_t)d, (uint64_t)p, 0, STREAM_PSO_INIT, a.seed, (uint64_t)m);
-    const double x = __dadd_rn(lo, __dmul_rn(span, unit53(r.w[0])));
-    const double v = __dmul_rn(span, __dsub_rn(__dmul_rn(2.0, unit53(r.w[1])), 1.0));
+    double x, v;
+    pso_start(a, m, p, d, lo, span, x, v);
     a.x[c * a.ld + d] = x;
     a.v[c * a.ld + d] = v;
     a.pbest_x[c * a.ld + d] = x;
@@ -138,15 +136,9 @@ __global__ __launch_bounds__(256) void pso_step_kernel(const PsoArgs a) {
       d = (int)(e - p * N);
     }
     const int64_t c = c0 + p;
-    const U64x4 r = philox4x64((uint64_t)d, (uint64_t)p, (uint64_t)t, STREAM_PSO_STEP, a.seed, (uint64_t)m);
-    const double r1 = unit53(r.w[0]), r2 = unit53(r.w[1]);
-    const double xi = a.x[c * ld + d];
-    double vel = __dmul_rn(a.inertia, a.v[c * ld + d]);
-    vel = __dadd_rn(vel, __dmul_rn(__dmul_rn(a.c1, r1), __dsub_rn(a.pbest_x[c * ld + d], xi)));
-    if (social) vel = __dadd_rn(vel, __dmul_rn(__dmul_rn(a.c2, r2), __dsub_rn(a.gbest_x[(int64_t)m * ld + d], xi)));
+    double xn = a.x[c * ld + d], vel = a.v[c * ld + d];
+    pso_move(a, t, m, p, d, social, a.pbest_x[c * ld + d], social ? a.gbest_x[(int64_t)m * ld + d] : 0.0, lo, hi, xn, vel);
     a.v[c * ld + d] = vel;
-    double xn = __dadd_rn(xi, vel);
-    xn = xn < lo ? lo : (xn > hi ? hi : xn);
     a.x[c * ld + d] = xn;
   }
 }

@@ -346,3 +346,64 @@ def test_adjoint_every_pole_count(D, orc, N):
             gerr = np.max(np.abs(g_th.cpu().numpy() - og[rows]), axis=1) / np.max(np.abs(og[rows]), axis=1)
             print(f"N={N} {plan.info()[0]}: max theta-gradient rel err {gerr.max():.2e}")
             assert gerr.max() <= 1e-6
+
+
+def _small_swarm(N, seed):
+    """Swarms that run as one launch: 1 and 2 candidates to several tiles of
+    them, spectra of odd lengths, the last material's targets not a number."""
+    g = np.random.default_rng(seed)
+    n_poles = np.array(N if np.ndim(N) else [N] * 5, np.int32)
+    Fm, per = [2 * n_poles[0] - 1, 33, 100, 65, 40], [1, 2, 13, 40, 3]
+    om = np.concatenate([W.log_grid(1e6, 1e10, max(f, 2))[:f] for f in Fm])
+    er, ei = 2 + g.random(len(om)), g.random(len(om))
+    er[-40:] = np.nan
+    return W.offsets(Fm), W.offsets(per), n_poles, om, er, ei
+
+
+@pytest.mark.parametrize("N", [1, 2, 4, 5, 6, 8, 11, (3, 11, 1, 3, 7)])
+def test_swarm_in_one_launch(D, N):
+    """A small swarm fit as one launch per pole count equals the same fit run
+    step by step bit for bit: state, bests, history, costs and status, with
+    iterations and without, eagerly and captured by the caller."""
+    import torch
+    f_off, c_off, n_poles, om, er, ei = _small_swarm(N, 3)
+    b = D.Batch(f_off, c_off, n_poles, om, _t(er), _t(ei))
+    ld, P, M = int(n_poles.max()) + 1, int(c_off[-1]), len(n_poles)
+    lb, ub = _t(np.full(M, -12.0)), _t(np.full(M, -6.0))
+    plan, steps = D.Plan(b), D.Plan(b)
+    steps.set_launch(D.LAUNCH_PERSISTENT)
+
+    def run(p, iters, graph=False, into=None):
+        sw = D.Swarm.empty(P, M, ld, iters + 1)
+        st = torch.full((P,), 77, dtype=torch.int8, device="cuda")
+        c = torch.empty(P, dtype=torch.float64, device="cuda")
+        out = [sw.x, sw.v, sw.pbest_x, sw.pbest_cost, sw.gbest_x, sw.gbest_cost, sw.gbest_idx, sw.history, c, st]
+        for t in out[:5]:
+            t.fill_(0.25)
+
+        def go():
+            D.pso_run(p, b, lb, ub, sw, iters, seed=9, use_graph=graph, cost=c, status=st)
+        return go, out
+
+    for iters in (0, 1, 6):
+        want_go, want = run(steps, iters)
+        want_go()
+        for graph in (False, True):
+            go, got = run(plan, iters, graph)
+            go()
+            torch.cuda.synchronize()
+            for k, (x, y) in enumerate(zip(got, want)):
+                assert np.array_equal(x.cpu().numpy(), y.cpu().numpy(), equal_nan=True), (iters, graph, k)
+    go, got = run(plan, 6)
+    go()
+    torch.cuda.synchronize()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        go()
+    for _ in range(3):
+        for t in got[:5]:
+            t.fill_(0.25)
+        g.replay()
+        torch.cuda.synchronize()
+        for x, y in zip(got, want):
+            assert np.array_equal(x.cpu().numpy(), y.cpu().numpy(), equal_nan=True)
