@@ -538,24 +538,24 @@ int debye_da_run(const debye_plan *plan, const debye_batch *b, int64_t ld, const
  * direction is not a descent direction) is steepest descent scaled so that its
  * largest component is at most 1; a step with no acceptable trial leaves theta
  * unchanged; pairs with s.y <= 1e-300 are not stored (the history keeps its
- * older pairs).  The trials of a step are evaluated in three batched
- * launches: the full step (alpha = 1) of every material, the next four
- * halvings of the materials whose full step failed, and the remaining trials
- * of those still undecided (the result is the one a sequential halving search
+ * older pairs).  The trials of a step are evaluated in one to
+ * four batched launches of the next largest alphas, each for the materials
+ * still undecided (few materials try many alphas at once, many the first two,
+ * then 4, 8 and 16; the result is the one a sequential halving search
  * returns).  A step with no acceptable trial leaves point, gradient and
  * history unchanged, so the material is left out of the later steps' launches
  * (its next steps would reject the same trials).
  *
- * The polish context owns every buffer (history, trials, gradients and the two
+ * The polish context owns every buffer (history, trials, gradients and the
  * evaluation plans); debye_polish_create is the set-up call that allocates.
  * `shape` must describe one candidate per material (cand_off[m] = m); the
  * batches passed later must have the same shape.  The other calls only enqueue
  * work on `stream`: no allocation, no synchronisation, so a step can be
  * captured into a HIP graph.  Calls with one context must not overlap.
  *   debye_polish_begin:  cost and gradient at theta, history emptied.
- *   debye_polish_step:   one step (direction -> full steps -> further
- *                        trials where needed -> selection -> gradient at the
- *                        accepted point -> history update);
+ *   debye_polish_step:   one step (direction -> trials and selection, stage by
+ *                        stage -> gradient at the accepted point -> history
+ *                        update);
  *                        cost_hist [M][steps+1] (may be NULL) receives the cost
  *                        before step `step` and, at step == steps-1, the cost
  *                        at the end.

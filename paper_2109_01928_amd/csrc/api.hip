@@ -81,6 +81,7 @@ struct SwarmGraph {
 struct debye_plan {
   SwarmGraph graph, de_graph, da_graph;
   int32_t M = 0, max_poles = 0;
+  int32_t live = 1;   // one candidate in so many is evaluated
   int64_t n_freq = 0, n_cand = 0;
   std::vector<int64_t> f_off, cand_off;
   std::vector<int32_t> n_poles;
@@ -140,7 +141,7 @@ int pick_split(const debye_plan &p, const Bucket &b) {
     const int64_t points = avg_f / (2 * sf);
     return points >= 16 || (points >= 12 && most * b.SP * 2 * sf <= 256);
   };
-  while (sf < max_sf && (b.n_cands * b.SP * sf + 63) / 64 < TARGET_WAVES && wider()) sf *= 2;
+  while (sf < max_sf && (b.n_cands / p.live * b.SP * sf + 63) / 64 < TARGET_WAVES && wider()) sf *= 2;
   // the SP > 1 path keeps each candidate's normal matrix in LDS: fewer
   // candidates per wave until two waves per SIMD fit
   const int lds = dfit::lds_bytes_per_candidate(b.N);
@@ -501,8 +502,9 @@ extern "C" {
 const char *debye_last_error(void) { return g_error.c_str(); }
 const char *debye_version(void) { return "debyefit 0.1 (gfx950, FP64)"; }
 
-int debye_plan_create(const debye_batch *shape, const int64_t *f_off_host, const int64_t *cand_off_host,
-                      const int32_t *n_poles_host, uint32_t flags, debye_plan **out) {
+// live: one candidate in so many is evaluated (the others' waves exit at once)
+static int plan_create(const debye_batch *shape, const int64_t *f_off_host, const int64_t *cand_off_host,
+                       const int32_t *n_poles_host, uint32_t flags, int32_t live, debye_plan **out) {
   if (!out) return fail(DEBYE_EINVAL, "out is NULL");
   *out = nullptr;
   int rc = check_batch(shape);
@@ -528,6 +530,7 @@ int debye_plan_create(const debye_batch *shape, const int64_t *f_off_host, const
 
   debye_plan *p = new debye_plan();
   p->M = M;
+  p->live = live;
   p->max_poles = maxN;
   p->n_freq = shape->n_freq;
   p->n_cand = shape->n_cand;
@@ -595,6 +598,11 @@ int debye_plan_create(const debye_batch *shape, const int64_t *f_off_host, const
   }
   *out = p;
   return DEBYE_OK;
+}
+
+int debye_plan_create(const debye_batch *shape, const int64_t *f_off_host, const int64_t *cand_off_host,
+                      const int32_t *n_poles_host, uint32_t flags, debye_plan **out) {
+  return plan_create(shape, f_off_host, cand_off_host, n_poles_host, flags, 1, out);
 }
 
 int debye_plan_destroy(debye_plan *p) {
@@ -1460,18 +1468,45 @@ int debye_da_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
 }
 
 // ---- L-BFGS polish: a context that owns the workspace and the plans (one
-// candidate per material, for the gradient and the full steps; ta and tb
-// trials per material, for the two later stages of the line search), so that
-// the calls below only enqueue work
-constexpr int32_t POLISH_STAGE_A = 4;   // halvings tried right after a failed full step
+// candidate per material for the gradient, and those of the line search's
+// stages), so that the calls below only enqueue work
+
+// Trials a material of the line search's stages.  A stage costs a launch that
+// is bound by latency up to a few thousand candidates, so few materials try
+// many halvings at once; from 1,024 materials on the 30 trials are tried 2, 4, 8
+// and 16 at a time, each stage for the materials still undecided.  Per step, 20
+// steps from a swarm's best (POLISH_FILL 512, 1,024, 2,048, 4,096): 256 materials
+// of 8 poles and 500 points 149, 136, 114, 112 us, 64 of 10 poles and 1,000
+// points 136, 130, 98, 98; 512 of 20 poles and 3,000 points 841, 835, 732, 844.
+constexpr int32_t POLISH_FILL = 2048;
+void polish_stages(int32_t M, int32_t T, int32_t *end) {
+  constexpr int LAST = dfit::LBFGS_STAGES - 1;
+  int32_t n[LAST + 1] = {}, left = T;
+  for (int s = 0; s <= LAST; ++s) {
+    n[s] = std::min(left, std::max(s == 0 ? 1 : 2 << s, (POLISH_FILL << s) / M));
+    left -= n[s];
+    if (s == LAST || left < n[s] / 2) {   // no short stage for the rest
+      n[left >= n[s] / 2 ? LAST : n[1] > 0] += left;
+      break;
+    }
+  }
+  for (int s = 0; s < dfit::LBFGS_STAGES; ++s) end[s] = (s ? end[s - 1] : 0) + n[s];
+}
+// About one candidate in so many is still evaluated in a stage: its frequencies
+// are split as widely as for so many fewer, else a few wavefronts each run long.
+// Per step, 20 steps from a swarm's best, with all of them counted and so: 1,024
+// materials of 12 poles and 2,000 points 929 and 505 us, 8,192 of 6 poles and 500
+// points 921 and 367.
+constexpr int32_t POLISH_LIVE[dfit::LBFGS_STAGES] = {1, 4, 8, 16};
 
 struct debye_polish {
-  int32_t M = 0, max_poles = 0, mem = 0, max_trials = 0, steps = 0, ta = 0, tb = 0;
+  int32_t M = 0, max_poles = 0, mem = 0, max_trials = 0, steps = 0;
+  int32_t stage_end[dfit::LBFGS_STAGES] = {};
   int64_t ld = 0, n_freq = 0;
   double c1 = 0;
-  debye_plan *p1 = nullptr, *pA = nullptr, *pB = nullptr;
+  debye_plan *p1 = nullptr, *trials[dfit::LBFGS_STAGES] = {};   // (NULL: no trials in the stage)
   void *ws = nullptr;         // one allocation for every buffer below
-  int64_t *off_a = nullptr, *off_b = nullptr;   // [M+1] candidate offsets of the two later stages
+  int64_t *offs = nullptr;    // [M+1] candidate offsets of each stage
   double *grad, *S, *Y, *rho, *dir, *gd, *trial_theta, *trial_cost, *new_theta, *new_cost, *new_grad, *cost, *acc_cost;
   int32_t *hist_n, *hist_head, *accepted, *done, *stalled;
   int8_t *trial_status, *new_status;
@@ -1496,8 +1531,7 @@ dfit::LbfgsArgs polish_args(const debye_polish *pp, const debye_batch *b, double
   la.ld = pp->ld;
   la.mem = pp->mem;
   la.max_trials = pp->max_trials;
-  la.ta = pp->ta;
-  la.tb = pp->tb;
+  std::copy(pp->stage_end, pp->stage_end + dfit::LBFGS_STAGES, la.stage_end);
   la.c1 = pp->c1;
   la.lb = lb;
   la.ub = ub;
@@ -1543,20 +1577,19 @@ int debye_polish_create(const debye_batch *shape, const int64_t *f_off_host, con
                 DFIT_MAX_MEM);
   const int32_t M = shape->n_mat;
   const int T = lp.max_trials;
-  const int32_t ta = std::min(POLISH_STAGE_A, T - 1), tb = T - 1 - ta;
-  std::vector<int64_t> one(M + 1), offs_a(M + 1), offs_b(M + 1);
+  constexpr int STAGES = dfit::LBFGS_STAGES;
+  debye_polish *pp = new debye_polish();
+  polish_stages(M, T, pp->stage_end);
+  std::vector<int64_t> one(M + 1), offs((size_t)STAGES * (M + 1));
   for (int32_t m = 0; m <= M; ++m) {
     one[m] = m;
-    offs_a[m] = (int64_t)m * ta;
-    offs_b[m] = (int64_t)m * tb;
+    for (int s = 0; s < STAGES; ++s)
+      offs[(size_t)s * (M + 1) + m] = (int64_t)m * (pp->stage_end[s] - (s ? pp->stage_end[s - 1] : 0));
   }
-  debye_polish *pp = new debye_polish();
   pp->M = M;
   pp->max_poles = shape->max_poles;
   pp->mem = lp.mem;
   pp->max_trials = T;
-  pp->ta = ta;
-  pp->tb = tb;
   pp->steps = lp.steps;
   pp->c1 = lp.c1;
   pp->ld = ld;
@@ -1569,14 +1602,13 @@ int debye_polish_create(const debye_batch *shape, const int64_t *f_off_host, con
   const size_t doubles = (size_t)(n1 /*grad*/ + 2 * (int64_t)M * lp.mem * ld /*S,Y*/ + (int64_t)M * lp.mem /*rho*/ +
                                   n1 /*dir*/ + M /*gd*/ + nT * ld /*trial theta*/ + nT /*trial cost*/ + n1 /*new theta*/ +
                                   M /*new cost*/ + n1 /*new grad*/ + M /*cost*/ + M /*accepted cost*/);
-  const size_t bytes = (size_t)2 * (M + 1) * 8 + doubles * 8 + (size_t)5 * M * 4 + (size_t)nT + (size_t)M + 64;
+  const size_t bytes = offs.size() * 8 + doubles * 8 + (size_t)5 * M * 4 + (size_t)nT + (size_t)M + 64;
   if (hipMalloc(&pp->ws, bytes) != hipSuccess) {
     pp->ws = nullptr;
     return bail(fail(DEBYE_ENOMEM, "polish workspace allocation failed"));
   }
-  pp->off_a = (int64_t *)pp->ws;
-  pp->off_b = pp->off_a + M + 1;
-  double *dp = (double *)(pp->off_b + M + 1);
+  pp->offs = (int64_t *)pp->ws;
+  double *dp = (double *)(pp->offs + offs.size());
   auto take = [&](int64_t n) {
     double *r = dp;
     dp += n;
@@ -1603,21 +1635,17 @@ int debye_polish_create(const debye_batch *shape, const int64_t *f_off_host, con
   pp->stalled = ip + 4 * M;
   pp->trial_status = (int8_t *)(ip + 5 * M);
   pp->new_status = pp->trial_status + nT;
-  if (hipMemcpy(pp->off_a, offs_a.data(), (M + 1) * 8, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(pp->off_b, offs_b.data(), (M + 1) * 8, hipMemcpyHostToDevice) != hipSuccess)
+  if (hipMemcpy(pp->offs, offs.data(), offs.size() * 8, hipMemcpyHostToDevice) != hipSuccess)
     return bail(fail(DEBYE_EHIP, "polish: upload of the trial offsets failed"));
   std::vector<int64_t> f_h(f_off_host, f_off_host + M + 1);
   if ((rc = debye_plan_create(shape, f_h.data(), one.data(), n_poles_host, 0, &pp->p1))) return bail(rc);
   debye_batch bt = *shape;
-  if (ta > 0) {
-    bt.cand_off = pp->off_a;
-    bt.n_cand = (int64_t)M * ta;
-    if ((rc = debye_plan_create(&bt, f_h.data(), offs_a.data(), n_poles_host, 0, &pp->pA))) return bail(rc);
-  }
-  if (tb > 0) {
-    bt.cand_off = pp->off_b;
-    bt.n_cand = (int64_t)M * tb;
-    if ((rc = debye_plan_create(&bt, f_h.data(), offs_b.data(), n_poles_host, 0, &pp->pB))) return bail(rc);
+  for (int s = 0; s < STAGES; ++s) {
+    const int64_t *host = offs.data() + (size_t)s * (M + 1);
+    if (host[M] == 0) continue;
+    bt.cand_off = pp->offs + (size_t)s * (M + 1);
+    bt.n_cand = host[M];
+    if ((rc = plan_create(&bt, f_h.data(), host, n_poles_host, 0, POLISH_LIVE[s], &pp->trials[s]))) return bail(rc);
   }
   *out = pp;
   return DEBYE_OK;
@@ -1626,8 +1654,7 @@ int debye_polish_create(const debye_batch *shape, const int64_t *f_off_host, con
 int debye_polish_destroy(debye_polish *pp) {
   if (!pp) return DEBYE_OK;
   debye_plan_destroy(pp->p1);
-  debye_plan_destroy(pp->pA);
-  debye_plan_destroy(pp->pB);
+  for (debye_plan *p : pp->trials) debye_plan_destroy(p);
   if (pp->ws) {
     (void)hipDeviceSynchronize();   // no work of the context may still read the workspace
     (void)hipFree(pp->ws);
@@ -1648,6 +1675,42 @@ int debye_polish_begin(debye_polish *pp, const debye_batch *b, const double *the
                              pp->new_status, stream);
 }
 
+namespace {
+// the step whose direction and trial points are there already; with `next` the
+// next step's are formed as well
+int polish_rest_of_step(debye_polish *pp, const debye_batch *b, dfit::LbfgsArgs la, double damping, uint32_t flags,
+                        bool next, hipStream_t stream) {
+  int rc;
+  debye_batch bt = *b;
+  int64_t row = 0;
+  int32_t t_lo = 0;
+  for (int s = 0; s < dfit::LBFGS_STAGES; ++s) {
+    const int32_t t_hi = pp->stage_end[s] - 1;
+    if (t_hi < t_lo) continue;
+    bt.cand_off = pp->offs + (size_t)s * (pp->M + 1);
+    bt.n_cand = (int64_t)pp->M * (t_hi + 1 - t_lo);
+    // The first stage leaves out the materials that no longer move.  One whose
+    // step found no acceptable trial is stalled for good: its point, gradient
+    // and history stay as they were, so every later step would rebuild the
+    // same trials and reject them again.
+    if ((rc = fit_eval_impl(pp->trials[s], &bt, pp->trial_theta + row * pp->ld, pp->ld, damping, flags,
+                            pp->trial_cost + row, nullptr, nullptr, pp->trial_status + row,
+                            s == 0 ? pp->stalled : pp->done, stream)))
+      return rc;
+    CHECK_HIP(dfit::launch_lbfgs_select(la, t_lo, t_hi, stream), "lbfgs select");
+    row += bt.n_cand;
+    t_lo = t_hi + 1;
+  }
+  // cost and gradient at the accepted points (the stalled materials, which
+  // accepted none, are left out)
+  if ((rc = fit_eval_grad_launch(pp->p1, b, pp->new_theta, pp->ld, damping, flags, nullptr, pp->new_cost, pp->new_grad,
+                                 nullptr, nullptr, pp->new_status, nullptr, 0, stream, pp->stalled)))
+    return rc;
+  CHECK_HIP(dfit::launch_lbfgs_update(la, next, stream), "lbfgs update");
+  return DEBYE_OK;
+}
+}  // namespace
+
 int debye_polish_step(debye_polish *pp, const debye_batch *b, double *theta, const double *lb, const double *ub,
                       double damping, uint32_t flags, int32_t step, double *cost_hist, hipStream_t stream) {
   int rc = polish_check(pp, b, damping, flags);
@@ -1657,43 +1720,8 @@ int debye_polish_step(debye_polish *pp, const debye_batch *b, double *theta, con
     return fail(DEBYE_ERANGE, "step %d outside 0..%d", step, pp->steps - 1);
   dfit::LbfgsArgs la = polish_args(pp, b, theta, lb, ub, cost_hist);
   la.step = step;
-  const int32_t M = pp->M;
-  const int64_t ld = pp->ld;
-  hipError_t e = dfit::launch_lbfgs_direction(la, stream);
-  if (e != hipSuccess) return hip_fail(e, "lbfgs direction");
-  // stage 0: the full step of every material still moving (rows 0 .. M-1 of
-  // the trial arrays).  A material whose step found no acceptable trial is
-  // stalled for good: its point, gradient and history stay as they were, so
-  // every later step would rebuild the same trials and reject them again.
-  if ((rc = fit_eval_impl(pp->p1, b, pp->trial_theta, ld, damping, flags, pp->trial_cost, nullptr, nullptr,
-                          pp->trial_status, pp->stalled, stream)))
-    return rc;
-  if ((e = dfit::launch_lbfgs_first(la, stream)) != hipSuccess) return hip_fail(e, "lbfgs first trial");
-  // stages A and B: the next ta halvings, then the rest, each only for the
-  // materials the earlier stages left undecided
-  debye_batch bt = *b;
-  int64_t row = M;
-  int32_t t_lo = 1;
-  for (int stage = 0; stage < 2; ++stage) {
-    const int32_t n = stage == 0 ? pp->ta : pp->tb;
-    if (n == 0) continue;
-    bt.cand_off = stage == 0 ? pp->off_a : pp->off_b;
-    bt.n_cand = (int64_t)M * n;
-    if ((rc = fit_eval_impl(stage == 0 ? pp->pA : pp->pB, &bt, pp->trial_theta + row * ld, ld, damping, flags,
-                            pp->trial_cost + row, nullptr, nullptr, pp->trial_status + row, pp->done, stream)))
-      return rc;
-    if ((e = dfit::launch_lbfgs_select(la, t_lo, t_lo + n - 1, stream)) != hipSuccess)
-      return hip_fail(e, "lbfgs select");
-    row += (int64_t)M * n;
-    t_lo += n;
-  }
-  // cost and gradient at the accepted points (the stalled materials, which
-  // accepted none, are left out)
-  if ((rc = fit_eval_grad_launch(pp->p1, b, pp->new_theta, pp->ld, damping, flags, nullptr, pp->new_cost, pp->new_grad,
-                                 nullptr, nullptr, pp->new_status, nullptr, 0, stream, pp->stalled)))
-    return rc;
-  if ((e = dfit::launch_lbfgs_update(la, stream)) != hipSuccess) return hip_fail(e, "lbfgs update");
-  return DEBYE_OK;
+  CHECK_HIP(dfit::launch_lbfgs_direction(la, stream), "lbfgs direction");
+  return polish_rest_of_step(pp, b, la, damping, flags, false, stream);
 }
 
 int debye_lbfgs_polish(debye_polish *pp, const debye_batch *b, double *theta, const double *lb, const double *ub,
@@ -1703,8 +1731,10 @@ int debye_lbfgs_polish(debye_polish *pp, const debye_batch *b, double *theta, co
   if (!theta || !lb || !ub) return fail(DEBYE_EINVAL, "NULL pointer");
   if (pp->steps == 0) return DEBYE_OK;
   if ((rc = debye_polish_begin(pp, b, theta, damping, flags, stream))) return rc;
-  for (int32_t s = 0; s < pp->steps; ++s)
-    if ((rc = debye_polish_step(pp, b, theta, lb, ub, damping, flags, s, cost_hist, stream))) return rc;
+  dfit::LbfgsArgs la = polish_args(pp, b, theta, lb, ub, cost_hist);
+  CHECK_HIP(dfit::launch_lbfgs_direction(la, stream), "lbfgs direction");
+  for (la.step = 0; la.step < pp->steps; ++la.step)
+    if ((rc = polish_rest_of_step(pp, b, la, damping, flags, la.step + 1 < pp->steps, stream))) return rc;
   return DEBYE_OK;
 }
 

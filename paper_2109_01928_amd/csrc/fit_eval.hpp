@@ -199,6 +199,7 @@ hipError_t launch_da_init(const DaArgs &a, int64_t n_cand, hipStream_t s);
 hipError_t launch_da_visit(const DaArgs &a, int64_t n_cand, hipStream_t s);
 hipError_t launch_da_accept(const DaArgs &a, hipStream_t s);
 
+constexpr int LBFGS_STAGES = 4;
 struct LbfgsArgs {
   int32_t M;
   const int32_t *n_poles;
@@ -214,10 +215,10 @@ struct LbfgsArgs {
   int32_t *hist_n, *hist_head;  // [M]
   double *dir;         // [M][ld]
   double *gd;          // [M] g.d of the chosen direction
-  // the trials of a step in three stages, rows of the trial arrays: the full
-  // step of material m at row m; trials 1 .. ta at M + m*ta + (t-1); trials
-  // ta+1 .. max_trials-1 at M + M*ta + m*tb + (t-1-ta), tb = max_trials-1-ta
-  int32_t ta, tb;
+  // the trials of a step in stages of stage_end[s-1] .. stage_end[s] - 1 (the
+  // last of them max_trials): trial t of material m in a stage of n trials
+  // from lo on is row M*lo + m*n + (t-lo) of the trial arrays
+  int32_t stage_end[LBFGS_STAGES];
   double *trial_theta; // [M*max_trials][ld]
   const double *trial_cost;  // [M*max_trials]
   const int8_t *trial_status;
@@ -232,8 +233,7 @@ struct LbfgsArgs {
   int32_t step, steps;
 };
 hipError_t launch_lbfgs_direction(const LbfgsArgs &a, hipStream_t s);
-hipError_t launch_lbfgs_first(const LbfgsArgs &a, hipStream_t s);
 hipError_t launch_lbfgs_select(const LbfgsArgs &a, int32_t t_lo, int32_t t_hi, hipStream_t s);
-hipError_t launch_lbfgs_update(const LbfgsArgs &a, hipStream_t s);
+hipError_t launch_lbfgs_update(const LbfgsArgs &a, bool next, hipStream_t s);
 
 }  // namespace dfit

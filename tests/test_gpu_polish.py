@@ -127,3 +127,44 @@ def test_theta_gradient_padding_is_zero(D, orc):
     for c in range(wl.P):
         assert np.all(g[c, npc[c]:] == 0.0), c
         assert np.all(np.isfinite(g[c, :npc[c]]))
+
+
+@pytest.mark.parametrize("M,T,N", [(1, 1, 1), (3, 30, 24), (40, 64, 3), (90, 6, 12), (300, 30, 11), (1100, 30, 2),
+                                   (1100, 64, 5)])
+def test_polish_line_search_stages(D, orc, M, T, N):
+    """The line search in stages, by the number of materials and trials: the
+    first step decides as the oracle's sequential search (history to the 1e-6
+    of the polish tests), steps past the memory's length run in one call equal
+    single steps bit for bit, and a material without a finite cost stays."""
+    import torch
+    wl = W.hn_cc(M=M, F=70, N=N, P=1, iters=0, seed=7)
+    er, ei = targets_oracle(orc, wl)
+    one = np.arange(M + 1)
+    g = np.random.default_rng(1)
+    lo, hi = float(wl.lb[0]), float(wl.ub[0])
+    th0 = np.zeros((M, N + 1))
+    th0[:, :N] = lo + (hi - lo) * (np.arange(N) + 0.25 + 0.5 * g.random((M, N))) / N
+    b1 = D.Batch(wl.f_off, one, wl.n_poles, wl.omega, _t(er), _t(ei))
+    lb, ub = _t(wl.lb), _t(wl.ub)
+    oth, ohist = orc.lbfgs(orc.Batch(wl.f_off, one, wl.n_poles, wl.omega, er, ei), th0, wl.lb, wl.ub, steps=1,
+                           max_trials=T)
+    hist = D.lbfgs_polish(b1, _t(th0), lb, ub, steps=1, max_trials=T).cpu().numpy()
+    np.testing.assert_allclose(hist, ohist, rtol=1e-6)
+    if M > 1:
+        er[-1] = np.nan
+        b1 = D.Batch(wl.f_off, one, wl.n_poles, wl.omega, _t(er), _t(ei))
+    K = 5
+    a, c = _t(th0), _t(th0)
+    ha = D.lbfgs_polish(b1, a, lb, ub, steps=K, mem=3, max_trials=T)
+    p = D.Polish(b1, N + 1, steps=K, mem=3, max_trials=T)
+    hc = torch.empty_like(ha)
+    p.begin(b1, c)
+    for k in range(K):
+        p.step(b1, c, lb, ub, k, cost_hist=hc)
+    torch.cuda.synchronize()
+    a, c, ha, hc = (x.cpu().numpy() for x in (a, c, ha, hc))
+    np.testing.assert_array_equal(a, c)
+    np.testing.assert_array_equal(ha, hc)
+    assert np.all(np.diff(ha[:M - 1 if M > 1 else 1], axis=1) <= 0)
+    if M > 1:
+        np.testing.assert_array_equal(a[-1], th0[-1])
