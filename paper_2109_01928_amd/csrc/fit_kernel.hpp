@@ -327,8 +327,13 @@ __device__ __forceinline__ void basis_R(double w2, const double *tau2, double *R
 // 1/d0 = d1 (r p23), 1/d1 = d0 (r p23), 1/d2 = d3 (r p01), 1/d3 = d2 (r p01):
 // three products and one reciprocal per four poles in place of two
 // reciprocals (a reciprocal occupies the FP64 pipe for four issue cycles and
-// its Newton step for three more).  Poles beyond the last full group of four
-// are paired as above.
+// its Newton step for three more).  Three poles beyond the last full group
+// form a group too (r = 1/(p01 d2), 1/d0 = d1 (r d2), 1/d1 = d0 (r d2), 1/d2 =
+// p01 r: one reciprocal in place of a pair's and a single pole's; 256
+// materials, F = 2,000: 128 candidates of N = 7 448 -> 434 us, 256 of N = 13
+// 1,889 -> 1,864, of N = 14 1,779 -> 1,753; not for the 11 poles of one lane,
+// whose forward kernel spills more with it, 670 -> 679 us); one or two are
+// taken as above.
 //
 // The product of four d can leave the double range (each d < 1e150), so a
 // group works on d scaled by a power of two s, fixed from the bound
@@ -338,7 +343,8 @@ __device__ __forceinline__ void basis_R(double w2, const double *tau2, double *R
 // place of 1, every intermediate is the unscaled value times an exact power
 // of two (the same roundings, barring underflow of tiny products, which the
 // scaled form suffers less); the group's basis values come out divided by
-// s, and s is applied with tau after the frequency sums.  Any smaller s of
+// s, and s is applied with tau after the frequency sums (a group of three, d0
+// d1 d2 < 1e450, the same with s^3 and s >= 2^-169).  Any smaller s of
 // the same form down to 2^-253 keeps these bounds, so a wave takes, per
 // group index, the smallest s of its lanes: s is then wave-uniform and the
 // fused add reads it from a scalar register (a third vector operand of a
@@ -349,7 +355,10 @@ constexpr double OMEGA_BOUND = 1e45;   // admissible angular frequencies: 0 < w 
 
 template <int NB> struct Groups {
   static constexpr int NQ = NB / 4;              // groups of four owned poles
-  static constexpr int NS = NQ > 0 ? NQ : 1;     // (array size)
+  static constexpr bool THREE = NB % 4 == 3 && NB < 11;   // and one of three
+  static constexpr int NG = NQ + THREE;
+  static constexpr int NS = NG > 0 ? NG : 1;     // (array size)
+  static constexpr int POLES = 4 * NQ + 3 * THREE;
 };
 
 // the largest k >= 0 of the wave (shifts and broadcasts over the rows of 16
@@ -372,12 +381,13 @@ __device__ __forceinline__ void group_scales(const double *tau2, int *kq, double
   kq[0] = 0;
   sq[0] = 1.0;
 #pragma unroll
-  for (int g = 0; g < Groups<NB>::NQ; ++g) {
+  for (int g = 0; g < Groups<NB>::NG; ++g) {
+    const int n = g < Groups<NB>::NQ ? 4 : 3;
     int e = 0;   // sum of the binary exponents: prod d(1e45) < 2^e
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < n; ++t)
       e += __builtin_amdgcn_frexp_exp(__builtin_fma(OMEGA_BOUND * OMEGA_BOUND, tau2[4 * g + t], 1.0));
-    int k = e > 990 ? (e - 990 + 3) >> 2 : 0;
+    int k = e > 990 ? (e - 990 + n - 1) / n : 0;
     // |log10 tau| <= 30 gives e <= 1996, k <= 252; the cap keeps a lane with
     // rejected input (its results are discarded) from scaling its wave's
     // valid lanes out of range
@@ -390,15 +400,15 @@ __device__ __forceinline__ void group_scales(const double *tau2, int *kq, double
 
 // scale of owned pole i (1 outside the groups)
 template <int NB> __device__ __forceinline__ double pole_scale(const double *sq, int i) {
-  return i < 4 * Groups<NB>::NQ ? sq[i / 4] : 1.0;
+  return i < Groups<NB>::POLES ? sq[i / 4] : 1.0;
 }
 
 // x * 2^(+-k) of owned pole i's group (exact)
 template <int NB> __device__ __forceinline__ double group_unscale(const int *kq, int i, double x) {
-  return i < 4 * Groups<NB>::NQ ? __builtin_amdgcn_ldexp(x, kq[i / 4]) : x;
+  return i < Groups<NB>::POLES ? __builtin_amdgcn_ldexp(x, kq[i / 4]) : x;
 }
 template <int NB> __device__ __forceinline__ double group_scale(const int *kq, int i, double x) {
-  return i < 4 * Groups<NB>::NQ ? __builtin_amdgcn_ldexp(x, -kq[i / 4]) : x;
+  return i < Groups<NB>::POLES ? __builtin_amdgcn_ldexp(x, -kq[i / 4]) : x;
 }
 
 // R / s of the owned poles (tau2s = tau^2 s)
@@ -417,7 +427,18 @@ __device__ __forceinline__ void basis_Rs(double w2, const double *tau2s, const d
     R[c + 2] = d3 * r23;
     R[c + 3] = d2 * r23;
   }
-  basis_R<NB - 4 * Groups<NB>::NQ>(w2, tau2s + 4 * Groups<NB>::NQ, R + 4 * Groups<NB>::NQ);
+  constexpr int C = 4 * Groups<NB>::NQ;
+  if constexpr (Groups<NB>::THREE) {
+    const double s = sq[Groups<NB>::NQ];
+    const double d0 = __builtin_fma(w2, tau2s[C], s), d1 = __builtin_fma(w2, tau2s[C + 1], s);
+    const double d2 = __builtin_fma(w2, tau2s[C + 2], s), p01 = d0 * d1;
+    const double r = rcp_nr(p01 * d2), r01 = r * d2;
+    R[C] = d1 * r01;
+    R[C + 1] = d0 * r01;
+    R[C + 2] = p01 * r;
+  } else {
+    basis_R<NB - C>(w2, tau2s + C, R + C);
+  }
 }
 
 // U / s with U = w R directly (the Gram pass needs no R): the factor w enters
@@ -441,6 +462,17 @@ __device__ __forceinline__ void basis_Us(double w, double w2, const double *tau2
     U[c + 3] = d2 * r23;
   }
   constexpr int C = 4 * Groups<NB>::NQ;
+  if constexpr (Groups<NB>::THREE) {
+    const double s = sq[Groups<NB>::NQ];
+    const double d0 = __builtin_fma(w2, tau2s[C], s), d1 = __builtin_fma(w2, tau2s[C + 1], s);
+    const double d2 = __builtin_fma(w2, tau2s[C + 2], s), p01 = d0 * d1;
+    // (r <= 2^759 at the wave's smallest scale, so w r cannot overflow)
+    const double rw = w * rcp_nr(p01 * d2), r01 = rw * d2;
+    U[C] = d1 * r01;
+    U[C + 1] = d0 * r01;
+    U[C + 2] = p01 * rw;
+    return;
+  }
 #pragma unroll
   for (int c = C; c + 1 < NB; c += 2) {
     const double d0 = __builtin_fma(w2, tau2s[c], 1.0), d1 = __builtin_fma(w2, tau2s[c + 1], 1.0);
@@ -451,9 +483,8 @@ __device__ __forceinline__ void basis_Us(double w, double w2, const double *tau2
   if constexpr ((NB - C) & 1) U[NB - 1] = w * rcp_nr(__builtin_fma(w2, tau2s[NB - 1], 1.0));
 }
 
-// Owned poles left over after the groups of four and the pairs: one (the
-// last) or none.
-template <int NB> constexpr bool odd_pole() { return ((NB - 4 * Groups<NB>::NQ) & 1) != 0; }
+// Owned poles left over after the groups and the pairs: one (the last) or none.
+template <int NB> constexpr bool odd_pole() { return ((NB - Groups<NB>::POLES) & 1) != 0; }
 
 // The basis at two points a and b (w2 = w^2).  With an odd last pole, that
 // pole's two values share one reciprocal, r = 1/(d_a d_b), R_a = d_b r,
@@ -1487,6 +1518,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile, c
       // spill registers.)
       constexpr int NQ = Groups<NB>::NQ;   // groups of four per owner
       constexpr int LO = NB - 4 * NQ;      // leftover poles per owner
+      static_assert(!Groups<NB>::THREE, "the owners' leftovers are taken in pairs");
       constexpr int H = 2 * NB;            // poles per lane
       constexpr int HP = SP / 2;           // owner pairs per candidate
       const int h = q % HP;

@@ -407,3 +407,8 @@ def test_swarm_in_one_launch(D, N):
         torch.cuda.synchronize()
         for x, y in zip(got, want):
             assert np.array_equal(x.cpu().numpy(), y.cpu().numpy(), equal_nan=True)
+
+
+@pytest.mark.parametrize("N", [3, 7, 14])
+def test_adjoint_groups_of_three(D, orc, N):
+    test_adjoint_mixed_scale_waves(D, orc, N)

@@ -452,3 +452,12 @@ def test_material_ranges(D, orc, F):
         if not np.isnan(oJ[s]).any():
             scale = np.abs(oJ[s]).max(axis=(0, 2))
             assert np.all(np.abs(J[s] - oJ[s]).max(axis=(0, 2)) <= 1e-12 * scale), m
+
+
+@pytest.mark.parametrize("N", [3, 7, 13, 14])
+def test_cost_parity_groups_of_three(D, orc, N):
+    """Three poles of a lane share a reciprocal (N = 3, 7; 13 and 14 on two
+    lanes, the former with a padded pole): scaled bands, rejected neighbours
+    and waves of mixed scale as for the groups of four."""
+    test_cost_parity_scaled_pole_groups(D, orc, N)
+    test_cost_parity_mixed_scale_waves(D, orc, N)
