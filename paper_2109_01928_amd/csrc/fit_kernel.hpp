@@ -1988,80 +1988,85 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile, c
 #pragma unroll
     for (int cI = 0; cI < NB; ++cI) mu[cI] = mt[cI] * invd_own[cI];
 
-    // ---- pass 4: basis derivatives against the residuals.  With x^2 R = 1 - R,
-    // dR/dtheta = -2 ln10 I^2 and dI/dtheta = ln10 I (2R - 1); ln10 is applied
-    // after the sums, and the dot products run over R with tau-scaled weights
-    // as in the forward passes.
-    double T1[NB], T2[NB], T3[NB], T4[NB], zt4[NB], mt4[NB], tv4[NB], tv4s[NB];
-#pragma unroll
-    for (int cI = 0; cI < NB; ++cI) {
-      T1[cI] = T2[cI] = T3[cI] = T4[cI] = 0.0;
-      tv4[cI] = tau_of(cI);
-      tv4s[cI] = tau2_of(cI);
-      zt4[cI] = zc[cI] * tv4[cI];
-      mt4[cI] = mu[cI] * tv4[cI];
-    }
-    each_point<WALK, 1>(spec, fl, SF, [&](double w, double er, double ei) {
-        double Rv[NB];
-        basis_R<NB>(w * w, tv4s, Rv);
-        double pr = 0.0, pi = 0.0, pz = 0.0, pm = 0.0;
-#pragma unroll
-        for (int cI = 0; cI < NB; ++cI) {
-          pr = __builtin_fma(wv_[cI], Rv[cI], pr);
-          pi = __builtin_fma(wt[cI], Rv[cI], pi);
-          pz = __builtin_fma(zt4[cI], Rv[cI], pz);
-          pm = __builtin_fma(mt4[cI], Rv[cI], pm);
-        }
-        const double rr = (er - einf) - group_sum<SP>(pr);
-        const double ri = __builtin_fma(-w, group_sum<SP>(pi), ei);
-        const double qz = __builtin_fma(-w, group_sum<SP>(pz), ei);
-        const double qm = w * group_sum<SP>(pm);
-        const double m2rr = -2.0 * rr;
-#pragma unroll
-        for (int cI = 0; cI < NB; ++cI) {
-          const double R = Rv[cI];
-          const double I = (w * tv4[cI]) * R;
-          const double dI = I * __builtin_fma(2.0, R, -1.0);
-          T1[cI] = __builtin_fma(I * m2rr, I, __builtin_fma(dI, ri, T1[cI]));
-          T2[cI] = __builtin_fma(dI, qz, T2[cI]);
-          T3[cI] = __builtin_fma(dI, qm, T3[cI]);
-          T4[cI] = __builtin_fma(dI, I, T4[cI]);
-        }
-    });
-    freq_sum_n<NB, SP, SP>(T1, SL);
-    freq_sum_n<NB, SP, SP>(T2, SL);
-    freq_sum_n<NB, SP, SP>(T3, SL);
-    freq_sum_n<NB, SP, SP>(T4, SL);
-#pragma unroll
-    for (int cI = 0; cI < NB; ++cI) {
-      T1[cI] = LN10 * T1[cI];
-      T2[cI] = LN10 * T2[cI];
-      T3[cI] = LN10 * T3[cI];
-      T4[cI] = LN10 * T4[cI];
-    }
-    if (writer) {
-      // padding entries of the row (poles beyond this material's count) are 0
-      if (q == 0 && a.grad_theta)
-        for (int64_t p = N; p < a.ld; ++p) a.grad_theta[c * a.ld + p] = 0.0;
+    // per-candidate record for the target gradient: [w | z | mu | tau | eps_inf, gc]
+    if (writer && a.record) {
+      double *rec = a.record + c * a.rec_ld;
 #pragma unroll
       for (int cI = 0; cI < NB; ++cI) {
         const int p = pole_of(q, cI);
         if (p >= N) continue;
-        double g = -2.0 * wv_[cI] * T1[cI] + mu[cI] * T2[cI] - zc[cI] * T3[cI] -
-                   2.0 * damping * mu[cI] * zc[cI] * T4[cI];
-        if (a.grad_theta) a.grad_theta[c * a.ld + p] = st == ST_OK ? gc * g : NAN;
-        // per-candidate record for the target gradient: [w | z | mu | tau | eps_inf, gc]
-        if (a.record) {
-          double *rec = a.record + c * a.rec_ld;
-          rec[p] = wv_[cI];
-          rec[N + p] = zc[cI];
-          rec[2 * N + p] = mu[cI];
-          rec[3 * N + p] = tv4[cI];
-          if (p == 0) {
-            rec[4 * N] = einf;
-            rec[4 * N + 1] = st == ST_OK ? gc : 0.0;
-          }
+        rec[p] = wv_[cI];
+        rec[N + p] = zc[cI];
+        rec[2 * N + p] = mu[cI];
+        rec[3 * N + p] = tau_of(cI);
+        if (p == 0) {
+          rec[4 * N] = einf;
+          rec[4 * N + 1] = st == ST_OK ? gc : 0.0;
         }
+      }
+    }
+
+    // ---- pass 4: basis derivatives against the residuals r', r'', q = eps'' -
+    // I z and I mu.  With x^2 R = 1 - R, dR/dtheta = -2 ln10 I^2 and dI/dtheta =
+    // ln10 I (2R - 1), so the gradient of pole i is, up to ln10, the sum of
+    // I (2R - 1) (-2 w r'' + mu q - z (I mu) - 2 lambda mu z I) + 4 w I^2 r'.
+    // tau and the group scales are applied after the sums: with R' = R / s and
+    // h = 2 s R'^2 - R', I = tau s w R' and I (2R - 1) = tau s w h.  Three sums a
+    // pole, what is known of the poles inside the first: two more would save an
+    // operation and spill (56 registers at N = 16).  Against tau inside the sums,
+    // reciprocals by pairs and four sums, adjoint of 128 candidates (N <= 11; 256
+    // beyond) of 256 materials, F = 2,000: N = 8 953 -> 910 us, N = 11 1,444 ->
+    // 1,288, N = 16 4,112 -> 3,961; N = 12, bound by the other passes, 3,040 ->
+    // 3,054, at F = 200 736 -> 716.
+    double T1[NB], T2[NB], T3[NB], wvs[NB], wts[NB], zts[NB], mts[NB];
+#pragma unroll
+    for (int cI = 0; cI < NB; ++cI) {
+      T1[cI] = T2[cI] = T3[cI] = 0.0;
+      wvs[cI] = wv_[cI] * pole_scale<NB>(sq, cI);
+      wts[cI] = wv_[cI] * ts[cI];
+      zts[cI] = zc[cI] * ts[cI];
+      mts[cI] = mu[cI] * ts[cI];
+    }
+    each_point<WALK, 1>(spec, fl, SF, [&](double w, double er, double ei) {
+        const double w2 = w * w;
+        double Rv[NB];
+        basis_Rs<NB>(w2, tau2s, sq, Rv);
+        double pr = 0.0, pi = 0.0, pz = 0.0, pm = 0.0;
+#pragma unroll
+        for (int cI = 0; cI < NB; ++cI) {
+          pr = __builtin_fma(wvs[cI], Rv[cI], pr);
+          pi = __builtin_fma(wts[cI], Rv[cI], pi);
+          pz = __builtin_fma(zts[cI], Rv[cI], pz);
+          pm = __builtin_fma(mts[cI], Rv[cI], pm);
+        }
+        const double w2rr = w2 * ((er - einf) - group_sum<SP>(pr));
+        const double w2ri = -2.0 * w * __builtin_fma(-w, group_sum<SP>(pi), ei);
+        const double wqz = w * __builtin_fma(-w, group_sum<SP>(pz), ei);
+        const double wqm = -w2 * group_sum<SP>(pm);
+#pragma unroll
+        for (int cI = 0; cI < NB; ++cI) {
+          const double R = Rv[cI], R2 = R * R;
+          const double h = __builtin_fma(2.0 * pole_scale<NB>(sq, cI), R2, -R);
+          const double v = __builtin_fma(wts[cI], w2ri, __builtin_fma(mts[cI], wqz, zts[cI] * wqm));
+          T1[cI] = __builtin_fma(v, h, T1[cI]);
+          T2[cI] = __builtin_fma(w2rr, R2, T2[cI]);
+          T3[cI] = __builtin_fma(w2 * R, h, T3[cI]);
+        }
+    });
+#pragma unroll
+    for (int cI = 0; cI < NB; ++cI) {
+      T1[cI] = __builtin_fma(4.0 * wts[cI] * ts[cI], T2[cI], T1[cI]);
+      T1[cI] = __builtin_fma(-2.0 * damping * mts[cI] * zts[cI], T3[cI], T1[cI]);
+    }
+    freq_sum_n<NB, SP, SP>(T1, SL);
+    if (writer && a.grad_theta) {
+      // padding entries of the row (poles beyond this material's count) are 0
+      if (q == 0)
+        for (int64_t p = N; p < a.ld; ++p) a.grad_theta[c * a.ld + p] = 0.0;
+#pragma unroll
+      for (int cI = 0; cI < NB; ++cI) {
+        const int p = pole_of(q, cI);
+        if (p < N) a.grad_theta[c * a.ld + p] = st == ST_OK ? gc * (LN10 * T1[cI]) : NAN;
       }
     }
   }
