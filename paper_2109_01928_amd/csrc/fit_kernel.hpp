@@ -861,11 +861,11 @@ __device__ __forceinline__ void unpark(const double *park, int cpw, int grp, dou
 // --------------------------------------------------------------------------
 // How (WALK): 0, a lane's own 64-bit index; 1, the same, wave-uniform (split 1:
 // scalar loads); 2, a wave-uniform point and a lane's own constant offset; 3,
-// a lane's own 32-bit offset; 4, a lane's own index into LDS.
+// a lane's own index into LDS.
 // point k
 template <int WALK> __device__ __forceinline__ double ld(const double *p, int64_t k) {
-  if constexpr (WALK == 4) return ((lds_cptr)p)[k];
-  else if constexpr (WALK >= 2) return *(const double *)((const char *)p + ((uint32_t)k << 3));
+  if constexpr (WALK == 3) return ((lds_cptr)p)[k];
+  else if constexpr (WALK == 2) return *(const double *)((const char *)p + ((uint32_t)k << 3));
   else return p[k];
 }
 // The first point of a pass that reads one point ahead, through the constant
@@ -875,8 +875,8 @@ template <int WALK> __device__ __forceinline__ double ld(const double *p, int64_
 // top of every trip (which would expose the load latency at each point).
 template <int WALK> __device__ __forceinline__ double ld_first(const double *p, int64_t k) {
   using cptr = const __attribute__((address_space(4))) double *;
-  if constexpr (WALK == 4) return ((lds_cptr)p)[k];
-  else if constexpr (WALK >= 2) return *(cptr)((const char *)p + ((uint32_t)k << 3));
+  if constexpr (WALK == 3) return ((lds_cptr)p)[k];
+  else if constexpr (WALK == 2) return *(cptr)((const char *)p + ((uint32_t)k << 3));
   else return ((cptr)p)[k];
 }
 // Uniform tiles with a frequency split: the wave's lanes walk together, so a
@@ -1107,10 +1107,7 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile, c
   using S = Shape<N, SP>;
   constexpr bool MF = S::MF;
   constexpr int NB = S::NB, NV = S::NV, NG = S::NG, D = S::D;
-  // (the one-lane adjoint at N = 11 spills 250 registers; with the reader's
-  // descriptors its compiled form gave wrong gradients, so it keeps a lane's
-  // own offsets)
-  constexpr int WALK = OWN ? 4 : UNI == 2 && GRAD && SP == 1 && N >= 11 ? 3 : UNI;
+  constexpr int WALK = OWN ? 3 : UNI;
   extern __shared__ double lds_block[];
   double *const lds_all = OWN ? own.lds : lds_block;
 
