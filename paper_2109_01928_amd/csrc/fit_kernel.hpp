@@ -1082,6 +1082,23 @@ template <int N, int SP, bool GRAD, int UNI> constexpr int waves_per_simd() {
   return (SP == 1 && N <= 6) ? 3 : 2;
 }
 
+// Pole split by pole count, measured per bucket on the ragged workload (each
+// pole count alone, autotuned frequency split): one lane per candidate up to
+// N = 11 (at N = 9..11 its register spills cost less than the DPP traffic and
+// the padded pole of the two-lane ring; at N = 12 they do not), two lanes up
+// to N = 14, four above, with the Gram matrix on the matrix cores (figures at
+// the top of the file; N = 14 at F = 2000 1.80 ms on two lanes, 1.95 on four).
+// The adjoint of long spectra keeps two lanes up to N = 16: its third and fourth
+// passes take four pole sums a point, which four lanes combine in two steps
+// each (N = 16, F = 2000: 3.97 ms on two lanes, 4.22 on four); short ones are
+// bound by the solves, which four lanes share (F = 200: 1.20 and 1.05 ms).  On
+// two lanes and four, 16,384 candidates: N = 15 at F = 500 303 and 290 us, 700 390
+// and 395, 769 419 and 431, 1,100 565 and 603; N = 16 at F = 600 355 and 342, 768
+// 427 and 428, 900 487 and 499, 1,100 576 and 604.  (512 candidates, which do not
+// fill the chip, are faster on four throughout: N = 15 at F = 1,100 84 and 66 us.)
+constexpr int pole_split_for(int n) { return n <= 11 ? 1 : (n <= 14 ? 2 : 4); }
+constexpr int pole_split_long_grad(int n) { return n <= 11 ? 1 : (n <= 16 ? 2 : 4); }
+
 // UNI (uniform tiles; the plan checks that every active lane of every tile
 // belongs to one material and that spectra hold fewer than 2^29 points):
 //   1: frequency split 1, so every lane of a wave reads the same point and
@@ -1135,7 +1152,9 @@ __device__ __forceinline__ void fit_tile(const FitArgs &a, const int64_t tile, c
   const int64_t c = active ? cand : 0;
   // a wave whose candidates all belong to materials marked done exits
   // before any work (wave-uniform: a block is one wave)
-  if constexpr (MF)   // (a wave of a split narrower than its lanes can hold padding alone)
+  // (a wave of tiles made for fewer frequency lanes than the kernel's, or for
+  // another pole split, can hold padding alone)
+  if constexpr (MF || SP != pole_split_for(N))
     if (__builtin_amdgcn_ballot_w64(active) == 0) return;
   if (a.skip_mat && __builtin_amdgcn_ballot_w64(active && a.skip_mat[mat] == 0) == 0) return;
 
@@ -2093,19 +2112,6 @@ void fit_dd_kernel(const FitArgs a) {
   if (j >= a.xcd_off[xcd + 1] - a.xcd_off[xcd]) return;
   fit_tile<N, SP, false, 0, true>(a, a.xcd_off[xcd] + j);
 }
-
-// Pole split by pole count, measured per bucket on the ragged workload (each
-// pole count alone, autotuned frequency split): one lane per candidate up to
-// N = 11 (at N = 9..11 its register spills cost less than the DPP traffic and
-// the padded pole of the two-lane ring; at N = 12 they do not), two lanes up
-// to N = 14, four above, with the Gram matrix on the matrix cores (figures at
-// the top of the file; N = 14 at F = 2000 1.80 ms on two lanes, 1.95 on four).
-// The adjoint of long spectra keeps two lanes up to N = 16: its third and fourth
-// passes take four pole sums a point, which four lanes combine in two steps
-// each (N = 16, F = 2000: 3.97 ms on two lanes, 4.22 on four); short ones are
-// bound by the solves, which four lanes share (F = 200: 1.20 and 1.05 ms).
-constexpr int pole_split_for(int n) { return n <= 11 ? 1 : (n <= 14 ? 2 : 4); }
-constexpr int pole_split_long_grad(int n) { return n <= 11 ? 1 : (n <= 16 ? 2 : 4); }
 
 // Blocks of a cost-kernel grid: eight times the longest of the 8 XCD tile
 // lists (block b runs tile b / 8 of XCD b % 8's list).

@@ -348,6 +348,44 @@ def test_adjoint_every_pole_count(D, orc, N):
             assert gerr.max() <= 1e-6
 
 
+@pytest.mark.parametrize("N,F", [(9, 50), (10, 50), (11, 50), (9, 1001), (10, 1001), (11, 1001), (15, 768), (15, 769),
+                                 (15, 1001), (16, 768), (16, 769), (16, 1001)])
+def test_adjoint_forms(D, orc, N, F):
+    """The adjoint where its registers spill most and where its form changes:
+    9 to 11 poles on one lane (spectra shorter than a candidate's lanes, long
+    ones with a remainder), 15 and 16 poles on either side of the spectrum
+    length that moves them from four lanes to two, on tiles made for one
+    frequency lane (some waves then hold padding alone) to the widest split,
+    whole waves of one material and shared ones; gradients of relaxation times
+    and targets against the oracle, tolerances of test_adjoint_matches_oracle."""
+    import torch
+    wl = small_uniform(2, F, N, 64, seed=900 + N + F)
+    er, ei = targets_oracle(orc, wl)
+    g = np.random.default_rng(N + F)
+    lo, hi = wl.lb[0], wl.ub[0]
+    theta = lo + (hi - lo) * (np.arange(N) + 0.25 + 0.5 * g.random((wl.P, N))) / N
+    for per in (64, 21):
+        rows = np.concatenate([np.arange(wl.cand_off[m], wl.cand_off[m] + per) for m in range(wl.M)])
+        cand_off, th = W.offsets([per] * wl.M), theta[rows]
+        gc = np.linspace(0.5, 2.0, len(rows))
+        ob = orc.Batch(wl.f_off, cand_off, wl.n_poles, wl.omega, er, ei)
+        _, og, ogr, ogi, ost = orc.fit_grad(ob, th, grad_cost=gc)
+        b = D.Batch(wl.f_off, cand_off, wl.n_poles, wl.omega, _t(er), _t(ei))
+        plan = D.Plan(b, target_grads=True)
+        for split in (1, 2, 4, 16) + ((64,) if N <= 11 else ()):
+            plan.set_freq_split(split)
+            _, gt, gr, gi, st = D.fit_eval_grad(plan, b, _t(th), grad_cost=_t(gc), targets=True)
+            torch.cuda.synchronize()
+            np.testing.assert_array_equal(st.cpu().numpy(), ost)
+            gerr = np.max(np.abs(gt.cpu().numpy() - og), axis=1) / np.max(np.abs(og), axis=1)
+            print(f"N={N} F={F} {plan.info()[0]}: max theta-gradient rel err {gerr.max():.2e}", flush=True)
+            assert gerr.max() <= 1e-6
+            for a, o in ((gr.cpu().numpy(), ogr), (gi.cpu().numpy(), ogi)):
+                for m in range(wl.M):
+                    s = slice(wl.f_off[m], wl.f_off[m + 1])
+                    assert np.max(np.abs(a[s] - o[s])) <= 1e-6 * np.max(np.abs(o[s]))
+
+
 def _small_swarm(N, seed):
     """Swarms that run as one launch: 1 and 2 candidates to several tiles of
     them, spectra of odd lengths, the last material's targets not a number."""
