@@ -1074,10 +1074,14 @@ __device__ __forceinline__ bool rational_cost_pass(const double *tau2, const dou
 // The kernel.  GRAD adds the adjoint (grad w.r.t. log10 tau, and per-candidate
 // records for the target gradient).
 // --------------------------------------------------------------------------
-// target waves per SIMD: bounds the register budget of each instantiation
-// (three for the small one-lane kernels, which fit 168 registers; two
-// elsewhere: the N = 12 two-lane kernels fit three waves with one point per
-// trip of the Gram pass, but two waves with two points per trip are faster)
+// target waves per SIMD: bounds the register budget of each instantiation.
+// Three for the small one-lane kernels (168 registers: the forward ones of up to
+// 5 poles and the adjoints of up to 4 hold all but a few of their values in
+// them, the adjoints of 6 keep 44 to 76 in scratch memory); two elsewhere: the N =
+// 12 two-lane kernels fit three waves with one point per trip of the Gram pass,
+// but two waves with two points per trip are faster.  At two (256 registers)
+// the one-lane kernels from 9 poles on and the general tiles from 17 keep 30 to
+// 220 in scratch memory.
 template <int N, int SP, bool GRAD, int UNI> constexpr int waves_per_simd() {
   return (SP == 1 && N <= 6) ? 3 : 2;
 }
