@@ -138,11 +138,11 @@ typedef struct debye_batch {
  * per-candidate adjoint records that debye_fit_eval_grad needs for target
  * gradients (n_cand x (4 max_poles + 2) doubles).  Every buffer a plan uses
  * is allocated here, so the evaluation calls never allocate.
- * With more than one pole count the buckets of an evaluation are forked from
- * the caller's stream onto up to four streams owned by the plan and joined
- * back before the call's work is complete on the caller's stream (under
- * stream capture they become parallel graph branches).  A plan is therefore
- * not to be used from two host threads at once. */
+ * With more than one pole count the buckets of an evaluation are spread over
+ * the caller's stream and up to three streams owned by the plan, forked from
+ * it and joined back before the call's work is complete on the caller's stream
+ * (under stream capture they become parallel graph branches).  A plan is
+ * therefore not to be used from two host threads at once. */
 typedef struct debye_plan debye_plan;
 
 /* plan flags */
@@ -159,9 +159,7 @@ int debye_plan_destroy(debye_plan *plan);
  * count n_poles (0 = all). Used by the autotuner and the tests.  Pole counts
  * split over four lanes (15 and more) keep at least four frequency lanes in the
  * kernel: a narrower split sets their tiles, each run as several waves, with
- * the results of split 4.  Re-tiling
- * (here or in debye_plan_autotune) makes the plan's next optimiser run
- * re-capture its graph.  Not while work of the plan is in flight. */
+ * the results of split 4.  Not while work of the plan is in flight. */
 int debye_plan_set_freq_split(debye_plan *plan, int32_t n_poles, int32_t split);
 
 /* How an evaluation of a plan with several pole counts is launched:
@@ -349,14 +347,12 @@ int debye_pso_step(const debye_batch *b, int64_t ld, const double *lb, const dou
  * per material.  A small fit (at most 1,024 wavefronts an evaluation, 4 a
  * material, N <= 11, the swarm's state and spectrum within a block's LDS, no
  * DEBYE_FLAG_DD_REFINE) runs as one launch per pole count, a block a material.
- * Otherwise, with use_graph != 0 and more than 16 pole counts, one iteration
- * (step -> evaluation -> iteration-counter increment) is captured once as a
- * HIP graph (kept in the plan and reused while the arguments are unchanged) and
- * replayed `iters` times on a stream owned by the plan, ordered after and before
- * `stream` by events; fewer launches an iteration cost less enqueued one by one.
- * Results are bit-identical either way.  With use_graph != 0 the stream must
- * not be under capture.  history needs
- * hist_ld >= iters + 1.  Calls with one plan must not overlap.
+ * Otherwise the iterations are enqueued step by step; with use_graph != 0, on a
+ * plan without a launch mode set or tuned, the evaluations of a small batch of
+ * four or more pole counts take the persistent launch.  Results are
+ * bit-identical either way.  With use_graph != 0 the stream must not be under
+ * capture.  history needs hist_ld >= iters + 1.  Calls with one plan must not
+ * overlap.
  * ------------------------------------------------------------------------ */
 typedef struct debye_swarm {
   double *x, *v, *pbest_x;          /* [n_cand][ld] */
@@ -445,9 +441,8 @@ int debye_fit_auto(const debye_batch *mats, const int64_t *f_off_host, const dou
  *                    NULL).  Generation 0 is the initial population: call it
  *                    with u = x and cost_u = cost(x).
  *   debye_de_run:    init, generation 0, then `iters` generations, each
- *                    [trial -> debye_fit_eval -> select]; with use_graph and
- *                    more than 16 pole counts the generation is captured once
- *                    into a HIP graph and replayed (bit-identical).  history needs
+ *                    [trial -> debye_fit_eval -> select]; use_graph as in
+ *                    debye_pso_run (bit-identical).  history needs
  *                    hist_ld >= iters + 1.  Calls with one plan must not overlap.
  * All pointers are device pointers; rows have stride ld >= max_poles.
  * ------------------------------------------------------------------------ */
@@ -505,8 +500,8 @@ int debye_de_run(const debye_plan *plan, const debye_batch *b, int64_t ld, const
  *   debye_da_accept: generation t >= 1 as above; t = 0 takes y = x with
  *                    cost_y = cost(x) (the initial chains).
  *   debye_da_run:    init, generation 0, `iters` generations [visit ->
- *                    debye_fit_eval -> accept], replayed from a captured
- *                    HIP graph as debye_de_run (bit-identical); hist_ld >= iters + 1.
+ *                    debye_fit_eval -> accept]; use_graph as in
+ *                    debye_pso_run (bit-identical); hist_ld >= iters + 1.
  * Defaults of the method: qv = 2.62, qa = -5, t0 = 5230.
  * ------------------------------------------------------------------------ */
 typedef struct debye_da_params {

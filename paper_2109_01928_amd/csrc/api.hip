@@ -47,7 +47,7 @@ constexpr int64_t TARGET_WAVES = 2048;
 constexpr int LDS_PER_WAVE = 20 * 1024;
 // concurrent streams over which the pole-count buckets of one evaluation are
 // spread (one hardware queue each)
-constexpr int MAX_SIDE_STREAMS = 4;
+constexpr int MAX_STREAMS = 4;
 
 }  // namespace
 
@@ -68,18 +68,7 @@ struct Bucket {
   int32_t *d_lane_cand = nullptr, *d_lane_mat = nullptr, *d_mats = nullptr;
 };
 
-// a captured swarm iteration (step -> cost evaluation -> counter tick) and the
-// arguments it was captured with
-struct SwarmGraph {
-  hipGraphExec_t exec = nullptr;
-  hipStream_t stream = nullptr;
-  hipEvent_t ev_in = nullptr, ev_out = nullptr;
-  int32_t *counter = nullptr;
-  std::vector<unsigned char> key;
-};
-
 struct debye_plan {
-  SwarmGraph graph, de_graph, da_graph;
   int32_t M = 0, max_poles = 0;
   int32_t live = 1;   // one candidate in so many is evaluated
   int64_t n_freq = 0, n_cand = 0;
@@ -88,18 +77,19 @@ struct debye_plan {
   std::vector<Bucket> buckets;
   std::map<int32_t, int32_t> sf_override;  // N (0 = all) -> frequency split
   std::map<int32_t, int32_t> sf_tuned;     // N -> split measured fastest by debye_plan_autotune
-  uint64_t sched_gen = 0;                  // bumped by every tile rebuild; part of every graph key
   double *d_record = nullptr;
   int64_t rec_ld = 0;
-  // fork/join of the buckets over side streams: bucket i runs on side[lane_of[i]]
+  // fork/join of the buckets over the caller's stream and side streams: bucket
+  // i runs on the caller's (stream_of[i] == 0) or on side[stream_of[i] - 1]
   std::vector<hipStream_t> side;
   std::vector<hipEvent_t> ev_join;
   hipEvent_t ev_fork = nullptr;
   std::vector<int> stream_of;
   // several buckets: how an evaluation is launched (DEBYE_LAUNCH_*), whether
-  // the caller fixed it, and the persistent launch's tables
+  // the caller fixed it or the autotuner chose it, and the persistent launch's
+  // tables
   int32_t launch = DEBYE_LAUNCH_BUCKETS;
-  bool launch_fixed = false;
+  bool launch_fixed = false, launch_tuned = false;
   dfit::RaggedBucket *d_rbuckets = nullptr;
   int64_t *d_items = nullptr;
   int32_t *d_counters = nullptr;
@@ -223,8 +213,6 @@ Schedule make_schedule(const int64_t *f_off, const int64_t *cand_off, const std:
 }
 
 int build_tiles(debye_plan &p, Bucket &b) {
-  // captured graphs hold the old tile buffers: the new generation keys them out
-  ++p.sched_gen;
   free_bucket(b);
   b.SF = pick_split(p, b);
   b.lane_sf = std::max(b.SF, min_split(b.SP));
@@ -273,7 +261,6 @@ int build_ragged(debye_plan &p) {
   for (int x = 0; x < 9; ++x) p.item_off[x] = 0;
   p.ragged_lds = 0;
   if (p.buckets.size() < 2) return DEBYE_OK;
-  ++p.sched_gen;   // captured graphs hold the old tables
   std::vector<dfit::RaggedBucket> rb(p.buckets.size());
   std::vector<std::vector<std::pair<float, int64_t>>> per_xcd(8);
   for (size_t i = 0; i < p.buckets.size(); ++i) {
@@ -374,113 +361,50 @@ dfit::FitArgs fit_args(const debye_plan *p, const Bucket &bk, const debye_batch 
   return a;
 }
 
-// ---- captured optimiser iterations ----
-void graph_destroy(SwarmGraph &g) {
-  if (g.stream) (void)hipStreamSynchronize(g.stream);
-  if (g.exec) (void)hipGraphExecDestroy(g.exec);
-  if (g.ev_in) (void)hipEventDestroy(g.ev_in);
-  if (g.ev_out) (void)hipEventDestroy(g.ev_out);
-  if (g.stream) (void)hipStreamDestroy(g.stream);
-  if (g.counter) (void)hipFree(g.counter);
-  g = SwarmGraph();
+// ---- optimiser runs ----
+// How a run's evaluations are launched.  A small iteration over several pole
+// counts is bound by its launches, their fork and their join, so a run whose
+// caller left that to the library (use_graph, no launch mode set or tuned)
+// takes one persistent launch, with the same results, from four pole counts on
+// up to RUN_TILES tiles a pole count on average.  A generation of differential
+// evolution with a launch a bucket and with one for all: 3 pole counts 61 and 61
+// us at 24 tiles, 61 and 65 at 768; 4 pole counts 77 and 65 at 32, 78 and 70 at
+// 1,024, 78 and 94 at 2,048; 12 pole counts 132 and 101 at 104, 139 and 136 at
+// 3,328, 224 and 232 at 6,656; 24 pole counts 274 and 158 at 456, 407 and 666 at
+// 14,592.
+constexpr int64_t RUN_TILES = 256;
+int32_t run_launch(const debye_plan *p, int32_t use_graph) {
+  const int64_t counts = (int64_t)p->buckets.size();
+  if (!use_graph || p->launch_fixed || p->launch_tuned || counts < 4) return p->launch;
+  int64_t tiles = 0;
+  for (const Bucket &b : p->buckets) tiles += b.n_tiles;
+  return tiles <= RUN_TILES * counts ? DEBYE_LAUNCH_PERSISTENT : p->launch;
 }
 
-// move the work onto the graph's own stream (ordered after the caller's)
-int graph_enter(SwarmGraph &g, hipStream_t caller) {
-  if (!g.stream) {
-    CHECK_HIP(hipStreamCreateWithFlags(&g.stream, hipStreamNonBlocking), "graph stream");
-    CHECK_HIP(hipEventCreateWithFlags(&g.ev_in, hipEventDisableTiming), "graph event");
-    CHECK_HIP(hipEventCreateWithFlags(&g.ev_out, hipEventDisableTiming), "graph event");
-    if (hipMalloc(&g.counter, sizeof(int32_t)) != hipSuccess) return fail(DEBYE_ENOMEM, "graph counter");
-  }
-  CHECK_HIP(hipEventRecord(g.ev_in, caller), "event");
-  CHECK_HIP(hipStreamWaitEvent(g.stream, g.ev_in, 0), "event wait");
-  return DEBYE_OK;
+// use_graph on a stream under capture is refused
+int check_run_stream(int32_t use_graph, hipStream_t s) {
+  hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+  if (use_graph && hipStreamIsCapturing(s, &st) != hipSuccess) (void)hipGetLastError();
+  return st == hipStreamCaptureStatusNone ? DEBYE_OK
+                                          : fail(DEBYE_EHIP, "use_graph must be 0 on a stream under capture");
 }
-
-int graph_leave(SwarmGraph &g, hipStream_t caller) {
-  CHECK_HIP(hipEventRecord(g.ev_out, g.stream), "event");
-  CHECK_HIP(hipStreamWaitEvent(caller, g.ev_out, 0), "event wait");
-  return DEBYE_OK;
-}
-
-// Replay `iters` iterations of body(stream, counter) from one captured graph;
-// the device counter holds the iteration number, t0 for the first replay, and
-// the body ends with its increment.  The capture is reused while `key` (every
-// argument the captured nodes depend on) is unchanged.
-template <class BODY>
-int graph_replay(SwarmGraph &g, const std::vector<unsigned char> &key, int32_t t0, int32_t iters, BODY &&body) {
-  if (iters <= 0) return DEBYE_OK;
-  hipStream_t s = g.stream;
-  if (!g.exec || g.key != key) {
-    if (g.exec) {
-      (void)hipGraphExecDestroy(g.exec);
-      g.exec = nullptr;
-    }
-    hipGraph_t graph = nullptr;
-    CHECK_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal), "begin capture");
-    const int rc = body(s, g.counter);
-    const hipError_t e2 = rc ? hipSuccess : dfit::launch_tick(g.counter, s);
-    const hipError_t e3 = hipStreamEndCapture(s, &graph);
-    if (rc || e2 != hipSuccess || e3 != hipSuccess) {
-      if (graph) (void)hipGraphDestroy(graph);
-      return rc ? rc : hip_fail(e2 != hipSuccess ? e2 : e3, "graph capture");
-    }
-    const hipError_t e4 = hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0);
-    (void)hipGraphDestroy(graph);
-    if (e4 != hipSuccess) {
-      g.exec = nullptr;
-      return hip_fail(e4, "graph instantiate");
-    }
-    g.key = key;
-  }
-  CHECK_HIP(dfit::launch_set_counter(g.counter, t0, s), "counter");
-  for (int32_t t = 0; t < iters; ++t) CHECK_HIP(hipGraphLaunch(g.exec, s), "graph launch");
-  return DEBYE_OK;
-}
-
-// Whether an optimiser's iterations are replayed from a captured graph: with
-// few launches an iteration, enqueueing them costs less than the replay (its
-// nodes follow one another about 4 us apart, and it adds the counter's).  Per
-// iteration, replayed and enqueued: 8 materials of 64 particles (N = 12, 200
-// points) 56 and 46 us, 64 of 64 (N = 10, 300 points) 50 and 42, 12 ragged
-// materials with 9 pole counts 160 and 148.
-// A stream under capture keeps the replay, which it refuses.
-bool capturing(hipStream_t s) {
-  hipStreamCaptureStatus st;
-  return hipStreamIsCapturing(s, &st) == hipSuccess && st != hipStreamCaptureStatusNone;
-}
-bool replayed(const debye_plan *p, int32_t use_graph, hipStream_t s) {
-  return use_graph && (p->buckets.size() > 16 || capturing(s));
-}
-
-struct KeyBytes {
-  std::vector<unsigned char> v;
-  template <class T> void put(const T &x) {
-    const unsigned char *c = (const unsigned char *)&x;
-    v.insert(v.end(), c, c + sizeof(T));
-  }
-};
 
 // Enqueue launch(bucket, stream) for every non-empty bucket.  With several
-// buckets they fork from `stream` onto the plan's side streams and join back,
+// buckets some fork from `stream` onto the plan's side streams and join back,
 // so different pole counts overlap on the GPU; under stream capture the fork
-// and join become parallel branches of the graph.
+// and join become parallel branches of the graph.  The caller's stream takes its
+// share: each side stream costs the host a wait, a record and a wait more (with
+// all buckets on side streams a generation over 2 pole counts took 57 us, now
+// 42, over 9 123 and 103, over 24 391 and 226).
 template <class LAUNCH> int for_buckets(const debye_plan *p, hipStream_t stream, LAUNCH &&launch) {
-  if (p->side.empty()) {
-    for (const Bucket &bk : p->buckets)
-      if (bk.n_tiles) {
-        int rc = launch(bk, stream);
-        if (rc) return rc;
-      }
-    return DEBYE_OK;
-  }
   const int n_side = (int)p->side.size();
-  CHECK_HIP(hipEventRecord(p->ev_fork, stream), "fork event");
+  if (n_side) CHECK_HIP(hipEventRecord(p->ev_fork, stream), "fork event");
   for (int j = 0; j < n_side; ++j) CHECK_HIP(hipStreamWaitEvent(p->side[j], p->ev_fork, 0), "fork wait");
   int rc = DEBYE_OK;
-  for (size_t i = 0; i < p->buckets.size() && rc == DEBYE_OK; ++i)
-    if (p->buckets[i].n_tiles) rc = launch(p->buckets[i], p->side[p->stream_of[i]]);
+  for (size_t i = 0; i < p->buckets.size() && rc == DEBYE_OK; ++i) {
+    const int j = n_side ? p->stream_of[i] : 0;
+    if (p->buckets[i].n_tiles) rc = launch(p->buckets[i], j ? p->side[j - 1] : stream);
+  }
   // join every side stream, also after a failed launch, so no capture is left open
   for (int j = 0; j < n_side; ++j) {
     CHECK_HIP(hipEventRecord(p->ev_join[j], p->side[j]), "join event");
@@ -494,7 +418,7 @@ template <class LAUNCH> int for_buckets(const debye_plan *p, hipStream_t stream,
 namespace {
 int fit_eval_impl(const debye_plan *p, const debye_batch *b, const double *log10_tau, int64_t ld, double damping,
                   uint32_t flags, double *cost, double *weights, double *eps_inf, int8_t *status,
-                  const int32_t *skip_mat, hipStream_t stream);
+                  const int32_t *skip_mat, int32_t launch, hipStream_t stream);
 }  // namespace
 
 extern "C" {
@@ -575,10 +499,11 @@ static int plan_create(const debye_batch *shape, const int64_t *f_off_host, cons
     debye_plan_destroy(p);
     return rc;
   }
-  // several pole counts: the buckets run concurrently on side streams, each
-  // bucket (largest first) on the stream with the least work so far
-  const int n_side = std::min<int>(MAX_SIDE_STREAMS, (int)p->buckets.size());
-  if (n_side > 1) {
+  // several pole counts: the buckets run concurrently on the caller's stream
+  // and side streams, each bucket (largest first) on the one with the least
+  // work so far
+  const int n_side = std::min<int>(MAX_STREAMS, (int)p->buckets.size()) - 1;
+  if (n_side > 0) {
     p->side.assign(n_side, nullptr);
     p->ev_join.assign(n_side, nullptr);
     bool ok = hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming) == hipSuccess;
@@ -589,7 +514,7 @@ static int plan_create(const debye_batch *shape, const int64_t *f_off_host, cons
       debye_plan_destroy(p);
       return fail(DEBYE_EHIP, "plan: stream or event creation failed");
     }
-    std::vector<double> load(n_side, 0.0);
+    std::vector<double> load(n_side + 1, 0.0);
     for (const Bucket &b : p->buckets) {
       const int j = (int)(std::min_element(load.begin(), load.end()) - load.begin());
       p->stream_of.push_back(j);
@@ -607,9 +532,6 @@ int debye_plan_create(const debye_batch *shape, const int64_t *f_off_host, const
 
 int debye_plan_destroy(debye_plan *p) {
   if (!p) return DEBYE_OK;
-  graph_destroy(p->graph);
-  graph_destroy(p->de_graph);
-  graph_destroy(p->da_graph);
   for (hipStream_t st : p->side)
     if (st) (void)hipStreamSynchronize(st);
   for (auto &b : p->buckets) free_bucket(b);
@@ -643,8 +565,8 @@ int debye_plan_set_launch(debye_plan *p, int32_t mode) {
   if (mode != DEBYE_LAUNCH_AUTO && mode != DEBYE_LAUNCH_BUCKETS && mode != DEBYE_LAUNCH_PERSISTENT)
     return fail(DEBYE_EINVAL, "unknown launch mode %d", mode);
   p->launch_fixed = mode != DEBYE_LAUNCH_AUTO;
+  p->launch_tuned = false;
   const int32_t m = mode == DEBYE_LAUNCH_AUTO ? DEBYE_LAUNCH_BUCKETS : mode;
-  if (m != p->launch) ++p->sched_gen;
   p->launch = m;
   return DEBYE_OK;
 }
@@ -744,7 +666,7 @@ int debye_plan_autotune(debye_plan *p, const debye_batch *b, const double *log10
         best[m] = std::min(best[m], ms);
       }
     p->launch = best[1] < 0.97f * best[0] ? DEBYE_LAUNCH_PERSISTENT : DEBYE_LAUNCH_BUCKETS;
-    ++p->sched_gen;
+    p->launch_tuned = true;
   }
   return cleanup(DEBYE_OK);
 }
@@ -810,7 +732,8 @@ int debye_basis(const double *omega, int64_t F, const double *log10_tau, int64_t
 
 int debye_fit_eval(const debye_plan *p, const debye_batch *b, const double *log10_tau, int64_t ld, double damping,
                    uint32_t flags, double *cost, double *weights, double *eps_inf, int8_t *status, hipStream_t stream) {
-  return fit_eval_impl(p, b, log10_tau, ld, damping, flags, cost, weights, eps_inf, status, nullptr, stream);
+  return fit_eval_impl(p, b, log10_tau, ld, damping, flags, cost, weights, eps_inf, status, nullptr,
+                       p ? p->launch : DEBYE_LAUNCH_BUCKETS, stream);
 }
 
 }  // extern "C"
@@ -818,15 +741,15 @@ int debye_fit_eval(const debye_plan *p, const debye_batch *b, const double *log1
 namespace {
 // debye_fit_eval with an optional mask of materials to leave out ([M],
 // nonzero = skip: waves holding only such candidates exit at once and their
-// outputs are left as they were)
+// outputs are left as they were), in the given launch mode
 int fit_eval_impl(const debye_plan *p, const debye_batch *b, const double *log10_tau, int64_t ld, double damping,
                   uint32_t flags, double *cost, double *weights, double *eps_inf, int8_t *status,
-                  const int32_t *skip_mat, hipStream_t stream) {
+                  const int32_t *skip_mat, int32_t launch, hipStream_t stream) {
   int rc = check_plan_batch(p, b, ld);
   if (rc) return rc;
   if ((rc = check_damping(damping, flags))) return rc;
   if (!log10_tau || !cost) return fail(DEBYE_EINVAL, "log10_tau and cost must not be NULL");
-  if (p->launch == DEBYE_LAUNCH_PERSISTENT && p->buckets.size() > 1 && !(flags & DEBYE_FLAG_DD_REFINE)) {
+  if (launch == DEBYE_LAUNCH_PERSISTENT && p->buckets.size() > 1 && !(flags & DEBYE_FLAG_DD_REFINE)) {
     // one launch over every bucket, on the caller's stream
     dfit::RaggedArgs r{};
     r.common = fit_args(p, p->buckets[0], b, log10_tau, ld, damping, flags);
@@ -1114,10 +1037,10 @@ static dfit::PsoArgs pso_args(const debye_batch *b, int64_t ld, const double *lb
   return a;
 }
 
-int debye_pso_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const double *lb, const double *ub,
+int debye_pso_run(const debye_plan *plan, const debye_batch *b, int64_t ld, const double *lb, const double *ub,
                   debye_pso_params p, int32_t iters, double damping, uint32_t flags, const debye_swarm *sw,
                   int32_t use_graph, hipStream_t stream) {
-  int rc = check_plan_batch(pc, b, ld);
+  int rc = check_plan_batch(plan, b, ld);
   if (rc) return rc;
   if ((rc = check_damping(damping, flags))) return rc;
   if ((rc = pso_check(b, ld, lb, ub, p))) return rc;
@@ -1126,8 +1049,8 @@ int debye_pso_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const 
     return fail(DEBYE_EINVAL, "NULL swarm pointer");
   if (iters < 0) return fail(DEBYE_ERANGE, "iters must be >= 0");
   if (sw->history && sw->hist_ld < (int64_t)iters + 1) return fail(DEBYE_ERANGE, "hist_ld must be >= iters + 1");
-  debye_plan *plan = const_cast<debye_plan *>(pc);
-  if (swarm_in_one_launch(*plan, flags) && !(use_graph && capturing(stream)))
+  if ((rc = check_run_stream(use_graph, stream))) return rc;
+  if (swarm_in_one_launch(*plan, flags))
     return for_buckets(plan, stream, [&](const Bucket &bk, hipStream_t bs) -> int {
       dfit::FitArgs fa = fit_args(plan, bk, b, sw->x, ld, damping, flags);
       fa.cost = sw->cost;
@@ -1139,43 +1062,18 @@ int debye_pso_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const 
                 "swarm launch");
       return DEBYE_OK;
     });
-  SwarmGraph &g = plan->graph;
-  hipStream_t s = stream;
-  const bool replay = replayed(plan, use_graph, stream);
-  if (replay) {
-    if ((rc = graph_enter(g, stream))) return rc;
-    s = g.stream;
+  const int32_t launch = run_launch(plan, use_graph);
+  auto eval = [&]() {
+    return fit_eval_impl(plan, b, sw->x, ld, damping, flags, sw->cost, nullptr, nullptr, sw->status, nullptr, launch,
+                         stream);
+  };
+  CHECK_HIP(dfit::launch_pso_init(pso_args(b, ld, lb, ub, p, 0, 0, sw), b->n_cand, stream), "swarm init");
+  if ((rc = eval())) return rc;
+  for (int32_t t = 1; t <= iters; ++t) {
+    CHECK_HIP(dfit::launch_pso_step(pso_args(b, ld, lb, ub, p, t, 1, sw), stream), "swarm step");
+    if ((rc = eval())) return rc;
   }
-  dfit::PsoArgs a0 = pso_args(b, ld, lb, ub, p, 0, 0, sw);
-  CHECK_HIP(dfit::launch_pso_init(a0, b->n_cand, s), "swarm init");
-  if ((rc = debye_fit_eval(plan, b, sw->x, ld, damping, flags, sw->cost, nullptr, nullptr, sw->status, s))) return rc;
-  if (!replay) {
-    for (int32_t t = 1; t <= iters; ++t) {
-      CHECK_HIP(dfit::launch_pso_step(pso_args(b, ld, lb, ub, p, t, 1, sw), s), "swarm step");
-      if ((rc = debye_fit_eval(plan, b, sw->x, ld, damping, flags, sw->cost, nullptr, nullptr, sw->status, s)))
-        return rc;
-    }
-  } else {
-    KeyBytes key;
-    key.put(*b);
-    key.put(ld);
-    key.put(lb);
-    key.put(ub);
-    key.put(p);
-    key.put(damping);
-    key.put(flags);
-    key.put(*sw);
-    key.put(plan->sched_gen);
-    rc = graph_replay(g, key.v, 1, iters, [&](hipStream_t gs, int32_t *counter) -> int {
-      dfit::PsoArgs a = pso_args(b, ld, lb, ub, p, 0, 1, sw);
-      a.t_dev = counter;
-      CHECK_HIP(dfit::launch_pso_step(a, gs), "swarm step");
-      return debye_fit_eval(plan, b, sw->x, ld, damping, flags, sw->cost, nullptr, nullptr, sw->status, gs);
-    });
-    if (rc) return rc;
-  }
-  CHECK_HIP(dfit::launch_pso_step(pso_args(b, ld, lb, ub, p, iters + 1, 0, sw), s), "final bests");
-  if (replay) return graph_leave(g, stream);
+  CHECK_HIP(dfit::launch_pso_step(pso_args(b, ld, lb, ub, p, iters + 1, 0, sw), stream), "final bests");
   return DEBYE_OK;
 }
 
@@ -1256,10 +1154,10 @@ int debye_de_select(const debye_batch *b, int64_t ld, int32_t t, const double *u
   return DEBYE_OK;
 }
 
-int debye_de_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const double *lb, const double *ub,
+int debye_de_run(const debye_plan *plan, const debye_batch *b, int64_t ld, const double *lb, const double *ub,
                  debye_de_params p, int32_t iters, double damping, uint32_t flags, const debye_population *pop,
                  int32_t use_graph, hipStream_t stream) {
-  int rc = check_plan_batch(pc, b, ld);
+  int rc = check_plan_batch(plan, b, ld);
   if (rc) return rc;
   if ((rc = check_damping(damping, flags))) return rc;
   if ((rc = de_check(b, ld, lb, ub, p))) return rc;
@@ -1267,14 +1165,12 @@ int debye_de_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
     return fail(DEBYE_EINVAL, "NULL population pointer");
   if (iters < 0) return fail(DEBYE_ERANGE, "iters must be >= 0");
   if (pop->history && pop->hist_ld < (int64_t)iters + 1) return fail(DEBYE_ERANGE, "hist_ld must be >= iters + 1");
-  debye_plan *plan = const_cast<debye_plan *>(pc);
-  SwarmGraph &g = plan->de_graph;
-  hipStream_t s = stream;
-  const bool replay = replayed(plan, use_graph, stream);
-  if (replay) {
-    if ((rc = graph_enter(g, stream))) return rc;
-    s = g.stream;
-  }
+  if ((rc = check_run_stream(use_graph, stream))) return rc;
+  const int32_t launch = run_launch(plan, use_graph);
+  auto eval = [&](const double *x) {
+    return fit_eval_impl(plan, b, x, ld, damping, flags, pop->cost, nullptr, nullptr, pop->status, nullptr, launch,
+                         stream);
+  };
   auto sel = [&](int32_t t) {
     dfit::DeArgs a = de_args(b, ld, lb, ub, p, t);
     a.u = pop->u;
@@ -1289,39 +1185,18 @@ int debye_de_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
     return a;
   };
   dfit::DeArgs a0 = sel(0);
-  CHECK_HIP(dfit::launch_de_init(a0, b->n_cand, s), "DE init");
+  CHECK_HIP(dfit::launch_de_init(a0, b->n_cand, stream), "DE init");
   // generation 0: the initial population is its own trial set
-  if ((rc = debye_fit_eval(plan, b, pop->x, ld, damping, flags, pop->cost, nullptr, nullptr, pop->status, s)))
-    return rc;
-  CHECK_HIP(hipMemcpyAsync(pop->u, pop->x, (size_t)b->n_cand * ld * 8, hipMemcpyDeviceToDevice, s), "copy");
-  CHECK_HIP(dfit::launch_de_select(a0, s), "DE select");
-  auto generation = [&](hipStream_t gs, int32_t t, const int32_t *t_dev) -> int {
-    dfit::DeArgs a = sel(t);
-    a.t_dev = t_dev;
-    CHECK_HIP(dfit::launch_de_trial(a, b->n_cand, gs), "DE trial");
-    int r = debye_fit_eval(plan, b, pop->u, ld, damping, flags, pop->cost, nullptr, nullptr, pop->status, gs);
-    if (r) return r;
-    CHECK_HIP(dfit::launch_de_select(a, gs), "DE select");
-    return DEBYE_OK;
-  };
-  if (!replay) {
-    for (int32_t t = 1; t <= iters; ++t)
-      if ((rc = generation(s, t, nullptr))) return rc;
-    return DEBYE_OK;
+  if ((rc = eval(pop->x))) return rc;
+  CHECK_HIP(hipMemcpyAsync(pop->u, pop->x, (size_t)b->n_cand * ld * 8, hipMemcpyDeviceToDevice, stream), "copy");
+  CHECK_HIP(dfit::launch_de_select(a0, stream), "DE select");
+  for (int32_t t = 1; t <= iters; ++t) {
+    const dfit::DeArgs a = sel(t);
+    CHECK_HIP(dfit::launch_de_trial(a, b->n_cand, stream), "DE trial");
+    if ((rc = eval(pop->u))) return rc;
+    CHECK_HIP(dfit::launch_de_select(a, stream), "DE select");
   }
-  KeyBytes key;
-  key.put(*b);
-  key.put(ld);
-  key.put(lb);
-  key.put(ub);
-  key.put(p);
-  key.put(damping);
-  key.put(flags);
-  key.put(*pop);
-  key.put(pc->sched_gen);
-  rc = graph_replay(g, key.v, 1, iters, [&](hipStream_t gs, int32_t *counter) { return generation(gs, 0, counter); });
-  if (rc) return rc;
-  return graph_leave(g, stream);
+  return DEBYE_OK;
 }
 
 // ---- annealing ----
@@ -1399,10 +1274,10 @@ int debye_da_accept(const debye_batch *b, int64_t ld, debye_da_params p, int32_t
   return DEBYE_OK;
 }
 
-int debye_da_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const double *lb, const double *ub,
+int debye_da_run(const debye_plan *plan, const debye_batch *b, int64_t ld, const double *lb, const double *ub,
                  debye_da_params p, int32_t iters, double damping, uint32_t flags, const debye_population *pop,
                  int32_t use_graph, hipStream_t stream) {
-  int rc = check_plan_batch(pc, b, ld);
+  int rc = check_plan_batch(plan, b, ld);
   if (rc) return rc;
   if ((rc = check_damping(damping, flags))) return rc;
   if ((rc = da_check(b, ld, p))) return rc;
@@ -1411,14 +1286,12 @@ int debye_da_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
     return fail(DEBYE_EINVAL, "NULL population pointer");
   if (iters < 0) return fail(DEBYE_ERANGE, "iters must be >= 0");
   if (pop->history && pop->hist_ld < (int64_t)iters + 1) return fail(DEBYE_ERANGE, "hist_ld must be >= iters + 1");
-  debye_plan *plan = const_cast<debye_plan *>(pc);
-  SwarmGraph &g = plan->da_graph;
-  hipStream_t s = stream;
-  const bool replay = replayed(plan, use_graph, stream);
-  if (replay) {
-    if ((rc = graph_enter(g, stream))) return rc;
-    s = g.stream;
-  }
+  if ((rc = check_run_stream(use_graph, stream))) return rc;
+  const int32_t launch = run_launch(plan, use_graph);
+  auto eval = [&](const double *x) {
+    return fit_eval_impl(plan, b, x, ld, damping, flags, pop->cost, nullptr, nullptr, pop->status, nullptr, launch,
+                         stream);
+  };
   auto args = [&](int32_t t) {
     dfit::DaArgs a = da_args(b, ld, lb, ub, p, t);
     a.u = pop->u;
@@ -1433,38 +1306,17 @@ int debye_da_run(const debye_plan *pc, const debye_batch *b, int64_t ld, const d
     return a;
   };
   dfit::DaArgs a0 = args(0);
-  CHECK_HIP(dfit::launch_da_init(a0, b->n_cand, s), "annealing init");
-  if ((rc = debye_fit_eval(plan, b, pop->x, ld, damping, flags, pop->cost, nullptr, nullptr, pop->status, s)))
-    return rc;
-  CHECK_HIP(hipMemcpyAsync(pop->u, pop->x, (size_t)b->n_cand * ld * 8, hipMemcpyDeviceToDevice, s), "copy");
-  CHECK_HIP(dfit::launch_da_accept(a0, s), "annealing accept");
-  auto generation = [&](hipStream_t gs, int32_t t, const int32_t *t_dev) -> int {
-    dfit::DaArgs a = args(t);
-    a.t_dev = t_dev;
-    CHECK_HIP(dfit::launch_da_visit(a, b->n_cand, gs), "annealing visit");
-    int r = debye_fit_eval(plan, b, pop->u, ld, damping, flags, pop->cost, nullptr, nullptr, pop->status, gs);
-    if (r) return r;
-    CHECK_HIP(dfit::launch_da_accept(a, gs), "annealing accept");
-    return DEBYE_OK;
-  };
-  if (!replay) {
-    for (int32_t t = 1; t <= iters; ++t)
-      if ((rc = generation(s, t, nullptr))) return rc;
-    return DEBYE_OK;
+  CHECK_HIP(dfit::launch_da_init(a0, b->n_cand, stream), "annealing init");
+  if ((rc = eval(pop->x))) return rc;
+  CHECK_HIP(hipMemcpyAsync(pop->u, pop->x, (size_t)b->n_cand * ld * 8, hipMemcpyDeviceToDevice, stream), "copy");
+  CHECK_HIP(dfit::launch_da_accept(a0, stream), "annealing accept");
+  for (int32_t t = 1; t <= iters; ++t) {
+    const dfit::DaArgs a = args(t);
+    CHECK_HIP(dfit::launch_da_visit(a, b->n_cand, stream), "annealing visit");
+    if ((rc = eval(pop->u))) return rc;
+    CHECK_HIP(dfit::launch_da_accept(a, stream), "annealing accept");
   }
-  KeyBytes key;
-  key.put(*b);
-  key.put(ld);
-  key.put(lb);
-  key.put(ub);
-  key.put(p);
-  key.put(damping);
-  key.put(flags);
-  key.put(*pop);
-  key.put(pc->sched_gen);
-  rc = graph_replay(g, key.v, 1, iters, [&](hipStream_t gs, int32_t *counter) { return generation(gs, 0, counter); });
-  if (rc) return rc;
-  return graph_leave(g, stream);
+  return DEBYE_OK;
 }
 
 // ---- L-BFGS polish: a context that owns the workspace and the plans (one
@@ -1695,7 +1547,7 @@ int polish_rest_of_step(debye_polish *pp, const debye_batch *b, dfit::LbfgsArgs 
     // same trials and reject them again.
     if ((rc = fit_eval_impl(pp->trials[s], &bt, pp->trial_theta + row * pp->ld, pp->ld, damping, flags,
                             pp->trial_cost + row, nullptr, nullptr, pp->trial_status + row,
-                            s == 0 ? pp->stalled : pp->done, stream)))
+                            s == 0 ? pp->stalled : pp->done, pp->trials[s]->launch, stream)))
       return rc;
     CHECK_HIP(dfit::launch_lbfgs_select(la, t_lo, t_hi, stream), "lbfgs select");
     row += bt.n_cand;

@@ -140,7 +140,7 @@ __global__ __launch_bounds__(256) void da_init_kernel(const DaArgs a, int64_t n_
 __global__ __launch_bounds__(256) void da_visit_kernel(const DaArgs a, int64_t n_cand) {
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n_cand) return;
-  const int32_t t = a.t_dev ? *a.t_dev : a.t;
+  const int32_t t = a.t;
   const int m = mat_of(a.cand_off, a.M, c);
   const int64_t i = c - a.cand_off[m];
   const Temps tp = temps(a.qv, a.t0, t);
@@ -159,7 +159,7 @@ __global__ __launch_bounds__(256) void da_accept_kernel(const DaArgs a) {
   __shared__ int s_take;
   const int m = blockIdx.x;
   const int tid = threadIdx.x;
-  const int32_t t = a.t_dev ? *a.t_dev : a.t;
+  const int32_t t = a.t;
   const int64_t c0 = a.cand_off[m];
   const int64_t P = a.cand_off[m + 1] - c0;
   const int N = a.n_poles[m];

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(256) void de_trial_kernel(const DeArgs a, int64_t n
 #pragma clang fp contract(off)
   const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (c >= n_cand) return;
-  const int32_t t = a.t_dev ? *a.t_dev : a.t;
+  const int32_t t = a.t;
   const int m = mat_of(a.cand_off, a.M, c);
   const int64_t c0 = a.cand_off[m];
   const int64_t P = a.cand_off[m + 1] - c0;
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(256) void de_select_kernel(const DeArgs a) {
   __shared__ int s_take;
   const int m = blockIdx.x;
   const int tid = threadIdx.x;
-  const int32_t t = a.t_dev ? *a.t_dev : a.t;
+  const int32_t t = a.t;
   const int64_t c0 = a.cand_off[m];
   const int64_t P = a.cand_off[m + 1] - c0;
   const int N = a.n_poles[m];

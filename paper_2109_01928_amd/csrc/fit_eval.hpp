@@ -102,7 +102,6 @@ struct PsoArgs {
   double inertia, c1, c2;
   uint64_t seed;
   int32_t t, move;
-  const int32_t *t_dev;  // if set, the iteration number is read from device memory
   const double *cost;
   double *x, *v, *pbest_x, *pbest_cost, *gbest_x, *gbest_cost;
   int64_t *gbest_idx;
@@ -120,11 +119,9 @@ hipError_t launch_swarm(int n, const FitArgs &fit, const PsoArgs &a, const int32
                         int32_t state_bytes, int32_t iters, hipStream_t s);
 hipError_t launch_pso_init(const PsoArgs &a, int64_t n_cand, hipStream_t s);
 hipError_t launch_pso_step(const PsoArgs &a, hipStream_t s);
-hipError_t launch_set_counter(int32_t *c, int32_t value, hipStream_t s);
 // p[0..n) = v (a kernel, so that it can sit in a captured graph)
 hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
-hipError_t launch_tick(int32_t *c, hipStream_t s);
 
 // error text for debye_last_error() (api.hip); returns code
 int set_error(int code, const char *msg);
@@ -163,7 +160,6 @@ struct DeArgs {
   double f_lo, f_hi, cr;
   uint64_t seed;
   int32_t t;
-  const int32_t *t_dev;  // if set, the generation number is read from device memory
   double *x, *u;         // population and trial vectors [n_cand][ld]
   const double *cost_u;  // cost of the trials
   double *fit;           // cost of the members
@@ -186,7 +182,6 @@ struct DaArgs {
   double qv, qa, t0;
   uint64_t seed;
   int32_t t;
-  const int32_t *t_dev;  // if set, the generation number is read from device memory
   double *x, *u;         // chain states and proposals [n_cand][ld]
   const double *cost_u;  // cost of the proposals
   double *fit;           // cost of the states

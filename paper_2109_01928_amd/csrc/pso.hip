@@ -57,7 +57,7 @@ __global__ __launch_bounds__(256) void pso_step_kernel(const PsoArgs a) {
   __shared__ int s_take;
   const int m = blockIdx.x;
   const int tid = threadIdx.x;
-  const int32_t t = a.t_dev ? *a.t_dev : a.t;
+  const int32_t t = a.t;
   const int64_t c0 = a.cand_off[m];
   const int64_t P = a.cand_off[m + 1] - c0;
   const int N = a.n_poles[m];
@@ -148,15 +148,6 @@ hipError_t launch_pso_step(const PsoArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-// iteration counter of a replayed swarm graph (a kernel, so that graphs hold
-// no memset nodes)
-__global__ void set_counter_kernel(int32_t *c, int32_t v) { *c = v; }
-__global__ void tick_kernel(int32_t *c) { *c = *c + 1; }
-
-hipError_t launch_set_counter(int32_t *c, int32_t value, hipStream_t s) {
-  hipLaunchKernelGGL(set_counter_kernel, dim3(1), dim3(1), 0, s, c, value);
-  return hipGetLastError();
-}
 __global__ __launch_bounds__(256) void fill_kernel(double *p, int64_t n, double v) {
   for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = v;
 }
@@ -176,11 +167,6 @@ hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s) {
   if (n <= 0) return hipSuccess;
   const int64_t blocks = std::min<int64_t>((n + 255) / 256, 4096);
   hipLaunchKernelGGL(fill_i32_kernel, dim3((unsigned)blocks), dim3(256), 0, s, p, n, v);
-  return hipGetLastError();
-}
-
-hipError_t launch_tick(int32_t *c, hipStream_t s) {
-  hipLaunchKernelGGL(tick_kernel, dim3(1), dim3(1), 0, s, c);
   return hipGetLastError();
 }
 

@@ -123,3 +123,92 @@ def test_gpu_swarm_fit_matches_oracle_swarm(D, orc):
           f"{first if first is not None else 'the end'}")
     assert same[: min(10, len(same))].all()
     assert gh[-1] <= oh[0] and abs(gh[-1] - oh[-1]) <= 0.05 * oh[-1]
+
+
+def _many_counts(orc, M=18, iters=5):
+    """One small material of each pole count 1 .. M."""
+    wl = small_ragged(M, seed=61, Fr=(30, 200), Nr=(1, 1), Pr=(6, 40))
+    wl.n_poles = np.arange(1, M + 1, dtype=np.int32)
+    wl.iters = iters
+    er, ei = targets_oracle(orc, wl)
+    return wl, er, ei
+
+
+def _run(D, opt, plan, b, lb, ub, iters, use_graph):
+    import torch
+    if opt == "pso":
+        sw = D.Swarm.empty(b.P, b.M, b.max_poles, iters + 1)
+        sw.gbest_x.zero_()
+        cost = D.pso_run(plan, b, lb, ub, sw, iters, seed=5, use_graph=use_graph)
+        out = [sw.gbest_cost, sw.gbest_idx, sw.history, sw.pbest_cost, cost]
+    else:
+        pop = D.Population.empty(b.P, b.M, b.max_poles, iters + 1)
+        run = D.de_run if opt == "de" else D.da_run
+        run(plan, b, lb, ub, pop, iters, seed=5, use_graph=use_graph)
+        out = [pop.fit, pop.best_cost, pop.best_idx, pop.history]
+    torch.cuda.synchronize()
+    return [t.cpu().numpy() for t in out]
+
+
+@pytest.mark.parametrize("opt", ["pso", "de", "da"])
+def test_runs_over_many_pole_counts(D, orc, opt):
+    """A run over 18 pole counts gives the same results bit for bit whether the
+    library chooses how its evaluations are launched (use_graph), with a launch
+    a bucket, with the persistent launch, and after the tiles changed; runs
+    repeated with other work between."""
+    import torch
+    wl, er, ei = _many_counts(orc)
+    b = D.Batch(wl.f_off, wl.cand_off, wl.n_poles, wl.omega, _t(er), _t(ei))
+    lb, ub = _t(wl.lb), _t(wl.ub)
+    plan = D.Plan(b)
+    assert len(plan.info()) == 18
+    want = _run(D, opt, plan, b, lb, ub, wl.iters, False)
+    theta = _t(W.draw_theta(wl.cand_off, wl.n_poles, wl.lb, wl.ub, wl.ld, 2))
+    for rep in range(3):
+        for x, y in zip(_run(D, opt, plan, b, lb, ub, wl.iters, True), want):
+            assert np.array_equal(x, y, equal_nan=True), rep
+        assert torch.isfinite(D.fit_eval(plan, b, theta)[0]).any()
+    for mode in (D.LAUNCH_BUCKETS, D.LAUNCH_PERSISTENT):
+        plan.set_launch(mode)
+        for use_graph in (False, True):
+            for x, y in zip(_run(D, opt, plan, b, lb, ub, wl.iters, use_graph), want):
+                assert np.array_equal(x, y, equal_nan=True), (mode, use_graph)
+    plan.set_launch(D.LAUNCH_AUTO)
+    for change in ("split", "autotune"):
+        if change == "split":
+            plan.set_freq_split(4)
+        else:
+            plan.set_freq_split(0)
+            plan.autotune(b, theta, reps=1)
+        a, c = (_run(D, opt, plan, b, lb, ub, wl.iters, g) for g in (False, True))
+        for x, y in zip(a, c):
+            assert np.array_equal(x, y, equal_nan=True), change
+
+
+@pytest.mark.parametrize("M", [1, 18])
+def test_use_graph_is_refused_under_capture(D, orc, M):
+    """use_graph on a stream under capture is an error that leaves the capture
+    as it was; without it the run is captured, and replays equal the eager run."""
+    import torch
+    wl, er, ei = _many_counts(orc, M, iters=2)
+    b = D.Batch(wl.f_off, wl.cand_off, wl.n_poles, wl.omega, _t(er), _t(ei))
+    lb, ub = _t(wl.lb), _t(wl.ub)
+    plan = D.Plan(b)
+    plan.set_launch(D.LAUNCH_PERSISTENT)
+    sw = D.Swarm.empty(b.P, b.M, b.max_poles, 3)
+    pop = D.Population.empty(b.P, b.M, b.max_poles, 3)
+    cost = torch.empty(b.P, dtype=torch.float64, device="cuda")
+    D.pso_run(plan, b, lb, ub, sw, 2, seed=5, use_graph=False, cost=cost)
+    torch.cuda.synchronize()
+    want = sw.history.cpu().numpy()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for run, state in ((D.pso_run, sw), (D.de_run, pop), (D.da_run, pop)):
+            with pytest.raises(D.DebyeError, match="under capture"):
+                run(plan, b, lb, ub, state, 2, seed=5, use_graph=True)
+        D.pso_run(plan, b, lb, ub, sw, 2, seed=5, use_graph=False, cost=cost)
+    for rep in range(3):
+        sw.history.fill_(-1.0)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(sw.history.cpu().numpy(), want), rep
