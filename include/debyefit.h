@@ -344,9 +344,10 @@ int debye_pso_step(const debye_batch *b, int64_t ld, const double *lb, const dou
 /* ------------------------------------------------------------------------
  * A whole swarm fit: pso_init, cost evaluation, then `iters` x (pso_step with
  * move, cost evaluation), then a bests-only pso_step; P*(iters+1) evaluations
- * per material.  A small fit (at most 1,024 wavefronts an evaluation, 4 a
- * material, N <= 11, the swarm's state and spectrum within a block's LDS, no
- * DEBYE_FLAG_DD_REFINE) runs as one launch per pole count, a block a material.
+ * per material.  A small fit (N <= 11, at most 4 wavefronts a material, the
+ * swarm's state and spectrum within a block's LDS, the blocks of all materials
+ * resident on the chip at once, no DEBYE_FLAG_DD_REFINE) runs as one launch per
+ * pole count, a block a material.
  * Otherwise the iterations are enqueued step by step; with use_graph != 0, on a
  * plan without a launch mode set or tuned, the evaluations of a small batch of
  * four or more pole counts take the persistent launch.  Results are

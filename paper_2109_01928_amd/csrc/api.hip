@@ -863,21 +863,29 @@ int fit_eval_grad_external(const debye_plan *p, const debye_batch *b, const doub
 }  // namespace dfit
 
 namespace {
-// A swarm fit whose batch cannot fill the chip is bound by its launches: up to
-// SWARM_TILES wavefronts an evaluation (one for every SIMD) it runs as one
-// launch, a block a material (swarm.hip), where the block's wavefronts, one a
-// SIMD, take all of the material's tiles at once.  One-lane candidates only (N
-// <= 11): the tiles of several lanes keep too much in LDS for a swarm's state
-// to join them.  Per iteration, in one launch and step by step, 64 particles, F
-// = 100: 8 materials of 5 poles 17.5 and 24.0 us, of 11 poles 31.9 and 43.7;
-// 250 materials 19.3 and 25.7, 35.6 and 59.8; past the limit, 500 materials of
-// 8 poles 46.0 and 43.6.  With eight wavefronts a block (F = 200, 5 poles) it
-// would lose: 26.1 and 24.3.
-constexpr int64_t SWARM_TILES = 1024;
+// A swarm fit whose batch cannot fill the chip is bound by its launches: where
+// every material's block is resident at once it runs as one launch, a block a
+// material (swarm.hip), whose wavefronts, up to one a SIMD, take all of the
+// material's tiles at once.  One-lane candidates only (N <= 11): the tiles of
+// several lanes keep too much in LDS for a swarm's state to join them.
+//
+// Resident blocks of a CU, by what they measured against the steps (us an
+// iteration, one launch and step by step): from 6 poles on a wavefront a SIMD
+// (the kernel's registers allow no second), 1,024 materials of 3 particles, N = 8,
+// F = 50 16 and 23, 1,400 31 and 25; 256 of 64 particles, F = 100 23 and 30, 300
+// 45 and 42; of 3 particles, F = 2,000 (three wavefronts) 30 and 38, 60 and 38.
+// Up to 5 poles two a SIMD: N = 5, 512 materials of 64 particles, F = 100 26 and
+// 32, 700 38 and 40, 1,400 72 and 64; blocks of one wavefront, which do not wait
+// for each other's rounds, up to three a SIMD: 3,000 materials of 3 particles, F =
+// 50 25 and 30, 4,096 32 and 33, 10,000 94 and 56.
+int64_t swarm_blocks(int N, int waves, int64_t lds) {
+  const int64_t by_waves = N > 5 ? 4 / waves : waves == 1 ? 12 : 8 / waves;
+  return std::min<int64_t>(by_waves, 160 * 1024 / (lds + 1024));   // (beside its static arrays)
+}
 
-// wavefronts of a block for the materials of bucket bk (0: step by step) and
-// the LDS of the largest one's state
-int swarm_waves(const debye_plan &p, const Bucket &bk, int64_t *state) {
+// wavefronts of a block for the materials of bucket bk (0: step by step), the
+// LDS of the largest one's state and of the block
+int swarm_waves(const debye_plan &p, const Bucket &bk, int64_t *state, int64_t *lds) {
   int64_t most = 0;
   *state = 0;
   if (bk.N > dfit::SWARM_POLES) return 0;
@@ -888,19 +896,22 @@ int swarm_waves(const debye_plan &p, const Bucket &bk, int64_t *state) {
     *state = std::max(*state, dfit::swarm_state_bytes(P, bk.N, F));
   }
   const int64_t per_wave = std::max<int64_t>(1, (int64_t)dfit::lds_bytes_per_candidate(bk.N) * bk.cpw);
-  return most <= dfit::SWARM_WAVES && most * per_wave + *state <= dfit::SWARM_LDS ? (int)most : 0;
+  *lds = most * per_wave + *state;
+  return most <= dfit::SWARM_WAVES && *lds <= dfit::SWARM_LDS ? (int)most : 0;
 }
 
 bool swarm_in_one_launch(const debye_plan &p, uint32_t flags) {
   if (p.launch != DEBYE_LAUNCH_BUCKETS || (flags & DEBYE_FLAG_DD_REFINE)) return false;
-  int64_t tiles = 0, state;
-  for (const Bucket &bk : p.buckets) tiles += bk.n_tiles;
-  if (tiles == 0 || tiles > SWARM_TILES) return false;
   for (int32_t m = 0; m < p.M; ++m)
     if (p.cand_off[m + 1] == p.cand_off[m]) return false;   // a swarm without particles
-  for (const Bucket &bk : p.buckets)
-    if (swarm_waves(p, bk, &state) == 0) return false;
-  return true;
+  double share = 0.0;   // of the chip's 256 CUs that the blocks of all buckets take
+  for (const Bucket &bk : p.buckets) {
+    int64_t state, lds;
+    const int waves = swarm_waves(p, bk, &state, &lds);
+    if (waves == 0) return false;
+    share += (double)bk.mats.size() / (256.0 * (double)swarm_blocks(bk.N, waves, lds));
+  }
+  return share > 0.0 && share <= 1.0;
 }
 }  // namespace
 
@@ -1055,8 +1066,8 @@ int debye_pso_run(const debye_plan *plan, const debye_batch *b, int64_t ld, cons
       dfit::FitArgs fa = fit_args(plan, bk, b, sw->x, ld, damping, flags);
       fa.cost = sw->cost;
       fa.status = sw->status;
-      int64_t state;
-      const int waves = swarm_waves(*plan, bk, &state);
+      int64_t state, lds;
+      const int waves = swarm_waves(*plan, bk, &state, &lds);
       CHECK_HIP(dfit::launch_swarm(bk.N, fa, pso_args(b, ld, lb, ub, p, 0, 1, sw), bk.d_mats, (int32_t)bk.mats.size(),
                                    waves, (int32_t)state, iters, bs),
                 "swarm launch");

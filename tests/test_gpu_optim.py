@@ -450,3 +450,32 @@ def test_swarm_in_one_launch(D, N):
 @pytest.mark.parametrize("N", [3, 7, 14])
 def test_adjoint_groups_of_three(D, orc, N):
     test_adjoint_mixed_scale_waves(D, orc, N)
+
+
+@pytest.mark.parametrize("M,P,F,N", [(10000, 3, 40, 5), (300, 3, 2000, 8), (256, 3, 2000, 8)])
+def test_one_launch_where_the_swarms_fit_the_chip(D, M, P, F, N):
+    """Many small swarms, or long spectra, whose blocks would not all be resident
+    keep to the steps (run as one launch these took 1.6 times the steps' time),
+    and one that just fits does not: the same results bit for bit, in at most
+    1.25 times the time of the steps."""
+    import time
+    import torch
+    g = np.random.default_rng(M)
+    om = np.tile(W.log_grid(1e6, 1e10, F), M)
+    b = D.Batch(W.offsets([F] * M), W.offsets([P] * M), np.full(M, N), om, _t(2 + g.random(M * F)), _t(g.random(M * F)))
+    lb, ub = _t(np.full(M, -12.0)), _t(np.full(M, -6.0))
+    plan, steps = D.Plan(b), D.Plan(b)
+    steps.set_launch(D.LAUNCH_PERSISTENT)
+    iters, best, out = 40, {}, {}
+    for name, p in (("plan", plan), ("steps", steps)) * 5:
+        sw = D.Swarm.empty(b.P, b.M, N, iters + 1)
+        torch.cuda.synchronize()
+        t = time.perf_counter()
+        cost = D.pso_run(p, b, lb, ub, sw, iters, seed=9)
+        torch.cuda.synchronize()
+        best[name] = min(best.get(name, np.inf), time.perf_counter() - t)
+        out[name] = [x.cpu().numpy() for x in (sw.x, sw.pbest_cost, sw.gbest_x, sw.gbest_cost, sw.history, cost)]
+    for x, y in zip(out["plan"], out["steps"]):
+        assert np.array_equal(x, y, equal_nan=True)
+    print({k: f"{v / iters * 1e6:.1f} us an iteration" for k, v in best.items()})
+    assert best["plan"] <= 1.25 * best["steps"]
