@@ -42,6 +42,12 @@ int hip_fail(hipError_t e, const char *what) {
 // Lanes per wave that the schedule tries to keep busy: the GPU has 256 CUs x 4
 // SIMDs; at two waves per SIMD a batch needs about 2048 waves to fill it.
 constexpr int64_t TARGET_WAVES = 2048;
+// Waves of a bucket (one for each SIMD) up to which lanes go below 16 points:
+// swarms of 32 particles and 100 points at split 4 and 8, forward (adjoint), us:
+// 8 poles at 1,000 waves 22.1 and 16.9 (33.4 and 24.2), 1,280 22.1 and 23.8 (33.4
+// and 35.8), 4,000 37 and 44 (56 and 68); 12 poles 36.7 and 33.5 (47.6 and 39.1) at
+// 1,000, 37.7 and 41.4 (48.5 and 49.5) at 1,520, 51 and 80 (65 and 97) at 4,000.
+constexpr int64_t SHORT_WAVES = 1024;
 // LDS budget of one single-wave block: a CU has 160 KiB, and two waves per SIMD
 // (eight per CU) need at most 20 KiB each
 constexpr int LDS_PER_WAVE = 20 * 1024;
@@ -122,16 +128,17 @@ int pick_split(const debye_plan &p, const Bucket &b) {
   // short spectra below 16 points per lane, or 12 where the swarms then still
   // have a wave for each SIMD of one CU (a block runs such a swarm whole: 40
   // particles of 5 poles and 50 points 11.6 us an iteration at split 4, 15.1 at 2,
-  // 12.8 at 8, whose fifth wave shares a SIMD)
+  // 12.8 at 8, whose fifth wave shares a SIMD) and the bucket at most SHORT_WAVES
   const int64_t avg_f = b.n_cands ? b.work / (b.n_cands * b.N) : 1;
   int64_t most = 0;   // candidates of the largest swarm
   for (int32_t m : b.mats) most = std::max(most, p.cand_off[m + 1] - p.cand_off[m]);
   int sf = min_split(b.SP);
+  auto waves = [&](int split) { return (b.n_cands / p.live * b.SP * split + 63) / 64; };
   auto wider = [&]() {
     const int64_t points = avg_f / (2 * sf);
-    return points >= 16 || (points >= 12 && most * b.SP * 2 * sf <= 256);
+    return points >= 16 || (points >= 12 && most * b.SP * 2 * sf <= 256 && waves(2 * sf) <= SHORT_WAVES);
   };
-  while (sf < max_sf && (b.n_cands / p.live * b.SP * sf + 63) / 64 < TARGET_WAVES && wider()) sf *= 2;
+  while (sf < max_sf && waves(sf) < TARGET_WAVES && wider()) sf *= 2;
   // the SP > 1 path keeps each candidate's normal matrix in LDS: fewer
   // candidates per wave until two waves per SIMD fit
   const int lds = dfit::lds_bytes_per_candidate(b.N);
