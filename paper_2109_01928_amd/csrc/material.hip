@@ -259,45 +259,55 @@ hipError_t launch_material_vjp(int32_t M, const int64_t *f_off, const double *ja
 
 // --------------------------------------------------------------------------
 // Debye basis materialised for inspection: re/im [n_cand][N][F] (coalesced
-// along F).  Bound by the bytes written (16 a value).  A block takes
-// BASIS_CHUNK points of one (candidate, pole) row, four a thread, so that
-// 10^theta (44 instructions) is raised once for four values; with one point a
-// thread it kept the FP64 pipe busy longer than the stores took: 1,024
-// candidates of 20 poles and 4,096 points (1.34 GB) 325 us, now 249 us (5.4
-// TB/s); of 8 poles and 1,000 points (131 MB) 25.3 and 24.7 us.  Streaming
-// stores take 232 us for the first and 26.8 us for the second.
+// along F).  Bound by the bytes written (16 a value).  A block takes 256 or 512
+// points of one (candidate, pole) row, one or two a thread: two, so that 10^theta
+// (44 instructions) is raised once for both; one for rows of a single block,
+// where a second would only cost registers.  Threads past the row's end leave
+// before the power.  With one point a thread, four and two: 1,024 candidates of
+// 20 poles and 4,096 points (1.34 GB) 320, 228 and 197 us (6.8 TB/s); of 8 poles
+// and 1,000 points (131 MB) 21.3, 21.1 and 20.7; 2,000 of 8 poles and 1,025
+// points 42, 54 and 40; 1,024 of 20 poles and 1,000 points 54, 61 and 58.  (A block
+// of four points a thread whose threads past the end raised the power too took
+// 94 us for 20,000 candidates of 5 poles and 50 points, now 49.)
 // --------------------------------------------------------------------------
-constexpr int BASIS_POINTS = 4, BASIS_CHUNK = 256 * BASIS_POINTS;
+constexpr int BASIS_POINTS = 2;   // of a thread where a row is longer than a block
 
+template <int POINTS>
 __global__ __launch_bounds__(256) void basis_kernel(const double *omega, int64_t F, const double *theta, int64_t ld,
-                                                   int64_t chunks, int64_t items, int32_t N, double *re, double *im) {
-  for (int64_t it = blockIdx.x; it < items; it += gridDim.x) {
-    const int64_t row = it / chunks;   // c * N + i
-    const int64_t k0 = (it - row * chunks) * BASIS_CHUNK + threadIdx.x;
-    const int64_t c = row / N;
-    const int i = (int)(row - c * N);
-    const double tau = exp10(theta[c * ld + i]);
-    double *r = re + row * F, *m = im + row * F;
+                                                   uint32_t N, double *re, double *im) {
+  const int64_t k0 = (int64_t)blockIdx.x * (256 * POINTS) + threadIdx.x;
+  if (k0 >= F) return;
+  const uint32_t row = blockIdx.y, c = row / N;   // row = c * N + i
+  const double tau = exp10(theta[c * ld + (row - c * N)]);
+  double *r = re + row * F, *m = im + row * F;
 #pragma unroll
-    for (int t = 0; t < BASIS_POINTS; ++t) {
-      const int64_t k = k0 + t * 256;
-      if (k < F) {
-        const double x = omega[k] * tau;
-        const double R = rcp_nr(__builtin_fma(x, x, 1.0));
-        r[k] = R;
-        m[k] = x * R;
-      }
+  for (int t = 0; t < POINTS; ++t) {
+    const int64_t k = k0 + t * 256;
+    if (k < F) {
+      const double x = omega[k] * tau;
+      const double R = rcp_nr(__builtin_fma(x, x, 1.0));
+      r[k] = R;
+      m[k] = x * R;
     }
   }
 }
 
 hipError_t launch_basis(const double *omega, int64_t F, const double *theta, int64_t ld, int64_t n_cand, int32_t N,
                         double *re, double *im, hipStream_t s) {
-  const int64_t chunks = (F + BASIS_CHUNK - 1) / BASIS_CHUNK, items = n_cand * N * chunks;
-  const int64_t blocks = items < (1 << 22) ? items : 1 << 22;   // (a grid holds fewer than 2^32 threads)
-  hipLaunchKernelGGL(basis_kernel, dim3((unsigned)blocks), dim3(256), 0, s, omega, F, theta, ld, chunks, items, N, re,
-                     im);
-  return hipGetLastError();
+  const int points = F <= 256 ? 1 : BASIS_POINTS;
+  const dim3 blocks((unsigned)((F + 256 * points - 1) / (256 * points)));
+  const int64_t per_launch = 65535 / N;   // candidates whose rows fit the grid's second dimension
+  for (int64_t c = 0; c < n_cand; c += per_launch) {
+    const dim3 grid(blocks.x, (unsigned)((n_cand - c < per_launch ? n_cand - c : per_launch) * N));
+    double *r = re + c * N * F, *m = im + c * N * F;
+    if (points == 1)
+      hipLaunchKernelGGL(basis_kernel<1>, grid, dim3(256), 0, s, omega, F, theta + c * ld, ld, (uint32_t)N, r, m);
+    else
+      hipLaunchKernelGGL(basis_kernel<BASIS_POINTS>, grid, dim3(256), 0, s, omega, F, theta + c * ld, ld, (uint32_t)N, r, m);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
 }
 
 }  // namespace dfit

@@ -461,3 +461,21 @@ def test_cost_parity_groups_of_three(D, orc, N):
     and waves of mixed scale as for the groups of four."""
     test_cost_parity_scaled_pole_groups(D, orc, N)
     test_cost_parity_mixed_scale_waves(D, orc, N)
+
+
+@pytest.mark.parametrize("F,C,N", [(1, 2, 24), (256, 3, 2), (257, 3, 2), (511, 2, 3), (513, 2, 3), (33, 70000, 1),
+                                   (33, 3000, 24)])
+def test_basis_blocks(D, orc, F, C, N):
+    """The materialised basis around its blocks (256 points one a thread, 512 two)
+    and over more rows than one launch holds (65,535), at sampled candidates.  The
+    two 10^theta are within an ulp each (4.4e-16 between them, twice that in 1 +
+    x^2), and each side rounds four times more: 2e-15."""
+    import torch
+    om = W.log_grid(1e5, 1e11, max(F, 2))[:F]
+    theta = np.random.default_rng(F + C).uniform(-12.5, -6.0, (C, N + 1))
+    re, im = D.basis(torch.tensor(om, device="cuda"), torch.tensor(theta, device="cuda"), N)
+    re, im = re.cpu().numpy(), im.cpu().numpy()
+    for c in np.unique(np.linspace(0, C - 1, 200).astype(int)):
+        r0, i0 = orc.basis(om, theta[c, :N])
+        np.testing.assert_allclose(re[c], r0, rtol=2e-15, atol=0)
+        np.testing.assert_allclose(im[c], i0, rtol=2e-15, atol=0)
