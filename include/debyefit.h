@@ -536,8 +536,8 @@ int debye_da_run(const debye_plan *plan, const debye_batch *b, int64_t ld, const
  * unchanged; pairs with s.y <= 1e-300 are not stored (the history keeps its
  * older pairs).  The trials of a step are evaluated in one to
  * four batched launches of the next largest alphas, each for the materials
- * still undecided (few materials try many alphas at once, many the first two,
- * then 4, 8 and 16; the result is the one a sequential halving search
+ * still undecided (few materials try many alphas at once, 30 trials of more
+ * than 1,024 materials go 1, 5, 8 and 16 at a time; the result is the one a sequential halving search
  * returns).  A step with no acceptable trial leaves point, gradient and
  * history unchanged, so the material is left out of the later steps' launches
  * (its next steps would reject the same trials).

@@ -1343,11 +1343,16 @@ int debye_da_run(const debye_plan *plan, const debye_batch *b, int64_t ld, const
 
 // Trials a material of the line search's stages.  A stage costs a launch that
 // is bound by latency up to a few thousand candidates, so few materials try
-// many halvings at once; from 1,024 materials on the 30 trials are tried 2, 4, 8
-// and 16 at a time, each stage for the materials still undecided.  Per step, 20
-// steps from a swarm's best (POLISH_FILL 512, 1,024, 2,048, 4,096): 256 materials
-// of 8 poles and 500 points 149, 136, 114, 112 us, 64 of 10 poles and 1,000
-// points 136, 130, 98, 98; 512 of 20 poles and 3,000 points 841, 835, 732, 844.
+// many halvings at once; 30 trials are tried 2, 4, 8 and 16 at a time from 911
+// to 1,024 materials and 1, 5, 8 and 16 beyond, each stage for the materials still
+// undecided.  (2, 4, 8 and 16 beyond as well is no clear gain: per step, 2 steps,
+// 1,100 materials of 8 poles and 500 points 176 and 171 us, 4,096 317 and 304,
+// 65,536 of 200 points 1,953 and 2,007, 1,100 of 12 poles and 2,000 points 574 and
+// 590; 20 steps 146 and 146, 254 and 254, 1,652 and 1,681, 498 and 542.)  Per
+// step, 20 steps from a swarm's best (POLISH_FILL 512, 1,024, 2,048, 4,096): 256
+// materials of 8 poles and 500 points 149, 136, 114, 112 us, 64 of 10 poles and
+// 1,000 points 136, 130, 98, 98; 512 of 20 poles and 3,000 points 841, 835, 732,
+// 844.
 constexpr int32_t POLISH_FILL = 2048;
 void polish_stages(int32_t M, int32_t T, int32_t *end) {
   constexpr int LAST = dfit::LBFGS_STAGES - 1;

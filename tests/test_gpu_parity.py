@@ -479,3 +479,10 @@ def test_basis_blocks(D, orc, F, C, N):
         r0, i0 = orc.basis(om, theta[c, :N])
         np.testing.assert_allclose(re[c], r0, rtol=2e-15, atol=0)
         np.testing.assert_allclose(im[c], i0, rtol=2e-15, atol=0)
+
+
+@pytest.mark.parametrize("N", [15, 16])
+def test_split_below_four_lanes_at_fewest_poles(D, orc, N):
+    """The fewest pole counts on four lanes; their adjoint at these lengths too
+    (past 768 points it takes two, test_adjoint_forms)."""
+    test_split_below_four_lanes_runs_as_split_four(D, orc, N)
