@@ -388,7 +388,7 @@ def polish_leg(D, wl, er, ei, best, lb, ub, steps, stream):
 def shard_comparison(D, W, wl, er, ei, args):
     """Batched fit vs the plain per-material loop at equal final residual: the
     first `shard` materials fitted together (the chosen optimiser with the
-    workload's population and iteration count, graph-replayed, then the L-BFGS
+    workload's population and iteration count, enqueued at once, then the L-BFGS
     polish); then, for the swarm only, the first `per_material` of them, each
     material alone (its own plan and swarm,
     forward evaluations only, the host reading the best cost after every

@@ -10,7 +10,7 @@
 // scalar register: the compiler moves a constant addend into vector registers
 // before the fused multiply-add (two instructions more), and read from constant
 // memory the coefficients' loads are waited for (2,048 tables of 4,096 points
-// 299 us against 234, before the pairs below took it to 245).  Against 80-bit arithmetic the
+// 299 us against 234, before the pairs below took it to 225-245, by the machine).  Against 80-bit arithmetic the
 // relative errors of HN targets are 9.0e-17 (real) and 1.7e-16 (imaginary part)
 // rms and 7.5e-16 at most; with the library's functions 9.7e-17, 2.7e-16 and
 // 2.5e-15.

@@ -114,7 +114,7 @@ __device__ __forceinline__ HnOut hn_term(double w, double d_eps, double tau0, do
 // One thread per frequency point; bound by the FP64 pipe (an HN term takes six
 // elementary functions, the noise three and a Philox call).  With the library's
 // functions 2,048 tables of 4,096 points (two terms and noise each on average)
-// took 409 us, with those of elem.hpp 245 us; 4,096 mixed materials of 1,000
+// took 409 us, with those of elem.hpp 225-245 us (by the machine); 4,096 mixed materials of 1,000
 // points 97 and 49 us.  The Jacobian's ten values a point go through LDS, so that
 // the block writes its 20 KiB in order (a thread's own 80 bytes, store by store,
 // touched 64 lines each; the mixed materials with it 180 us, now 115).
